@@ -201,33 +201,38 @@ bool is_mixed(int precision) {
 nbody_tuning default_tuning(int precision) {
   nbody_tuning t;
   std::memset(&t, 0, sizeof t);
-  // measured on MI355X at N = 2^18 and 2^20: the mixed loop with FP64
-  // differences runs fastest with one i per lane fed from scalar registers
-  // (its FP64 records as SGPR operands), the double-single one with one i
-  // per lane from LDS (more waves in flight), the FP64 loop with two i per
-  // lane from scalar registers
-  t.variant = precision == NBODY_MIXED      ? NBODY_VARIANT_S1
-              : precision == NBODY_MIXED_DS ? NBODY_VARIANT_K1
-                                            : NBODY_VARIANT_S2;
+  // one i per lane from scalar registers in every precision: items of 64
+  // i-slots, which fill the chip where two i per lane leave it idle (FP64,
+  // full evaluations: 4.33 against 4.37 ms at 2^16, 69.0 against 68.6 ms at
+  // 2^18).  The lighter acceleration-only loops prefer two in the
+  // FP64-difference form (1.82 against 2.12 ms at 2^16).
+  t.variant = NBODY_VARIANT_S1;
+  t.acc_variant = precision == NBODY_MIXED ? NBODY_VARIANT_S2 : 0;
   t.use_graph = NBODY_GRAPH_ON;
   t.steps_per_launch = 16;
   t.min_split_j = 256;
   t.refine_ratio = is_mixed(precision) ? kDefaultRefineRatio : -1.0f;
   t.near_jerk = is_mixed(precision) ? kDefaultNearJerk : -1.0f;
   t.small_log2 = kDefaultSmallLog2;
-  const int K = (t.variant == NBODY_VARIANT_K2) ? 2 : 1;
   for (int b = 0; b < NBODY_TUNE_BUCKETS; ++b) {
     // one i-tile covers the bucket [2^b, 2^(b+1)) when possible
-    int64_t cover = ((int64_t)2 << b) / K;
-    if (b == 0) cover = 1;
-    if (cover < 1) cover = 1;
     int P = 1;
-    while (P < cover && P < 256) P <<= 1;
+    while (P < ((int64_t)2 << b) && P < 256) P <<= 1;
+    if (b == 0) P = 1;
     t.i_slots[b] = P;
     // from 2^16 active particles on, split j as finely as the partial rows
     // allow: 2 MB chunks at N = 2^20, which each XCD's L2 holds while all
     // resident workgroups stream them
     t.target_items[b] = b >= 16 ? 131072 : 2048;
+    if (precision == NBODY_FP64) {
+      // as many slots as particles up to one wave, wide items from 2^11 on
+      // (N = 1024, every particle: 27 us a call where 256 slots, 8
+      // workgroups, took 73); about 2048 items from 64 particles on, 16 to
+      // 32 j-splits of a full evaluation (N = 2^14: 16 splits 301 us, 8 320,
+      // 32 311)
+      t.i_slots[b] = b < 6 ? 1 << b : (b < 11 ? 64 : 256);
+      t.target_items[b] = b < 6 ? 512 : b < 11 ? 2048 : b < 12 ? 512 : 1 << (b < 16 ? b - 2 : b - 3);
+    }
   }
   return t;
 }
@@ -286,7 +291,7 @@ struct nbody_ctx {
 
 namespace {
 
-nbk::Tuning device_tuning(const nbody_ctx *c, int K) {
+nbk::Tuning device_tuning(const nbody_ctx *c, int K, bool acc = false) {
   nbk::Tuning t{};
   for (int b = 0; b < nbk::kBuckets; ++b) {
     t.i_slots[b] = c->tune.i_slots[b];
@@ -294,6 +299,8 @@ nbk::Tuning device_tuning(const nbody_ctx *c, int K) {
   }
   t.min_split_j = c->tune.min_split_j;
   t.K = K;
+  t.fp64 = c->prec == NBODY_FP64 ? 1 : 0;
+  t.acc = acc ? 1 : 0;
   t.small_work = c->tune.small_log2 < 0 ? -1 : (int64_t)1 << c->tune.small_log2;
   return t;
 }
@@ -627,7 +634,7 @@ int api_forces(nbody_ctx *c, bool acc_only, const int32_t *i_active, int64_t n_a
   const int mode = acc_only ? acc_mode_of(c) : mode_of(c);
   const int grid = acc_only ? c->grid_acc_raw : c->grid_raw;
   const int K = acc_only ? c->Ka : c->K;
-  const nbk::Tuning t = device_tuning(c, K);
+  const nbk::Tuning t = device_tuning(c, K, acc_only);
   const int64_t cap = c->d.cap_active;
   for (int64_t k0 = 0; k0 < n_active; k0 += cap) {
     nbk::RawSrc r;
@@ -769,7 +776,7 @@ int nbody_step_symplectic(nbody_ctx *c, int scheme, double h, int64_t n_steps,
     w = {w3, w2, w1, w0, w1, w2, w3};
   }
   const int mode = acc_mode_of(c);
-  const nbk::Tuning t = device_tuning(c, c->Ka);
+  const nbk::Tuning t = device_tuning(c, c->Ka, true);
   // with one cluster the kernel before each evaluation (the all-active
   // setup, then every kick-drift) writes its plan
   NB_HIP(nbk::launch_all_active(c->d, t, c->stream));

@@ -11,6 +11,12 @@ namespace nbk {
 
 constexpr int kWG = 256;            // threads per workgroup of every kernel
 constexpr int kTJ = 256;            // j records per LDS tile of the force kernel
+constexpr int kBlk = 64;            // j per block of a wide item, and the
+                                    // i-slots of one whose waves share j
+constexpr int kFewItems = 256;      // fewer items of kWG slots than CUs: they
+                                    // are cut into four whatever their length
+constexpr int64_t kWideItems = 65536;   // from this many items of kWG slots on
+                                    // the waves of a wide item share i instead
 constexpr int kTickBits = 20;       // one time unit = 2^20 ticks
 constexpr int kLevels = 21;         // levels 0..20, step 2^-level
 constexpr int kMaxClusters = 4096;
@@ -59,7 +65,8 @@ enum Ctr : int {
 struct ClusterPlan {
   int32_t c;        // cluster id
   int32_t P;        // i thread-slots per workgroup (power of two, 1..256)
-  int32_t Qlog;     // log2 of j-lanes per i slot (Q = 256 / P)
+  int32_t Pt;       // i thread-slots of an item: P, or kBlk for wide items
+                    // (P = 256) whose waves share j
   int32_t S;        // j splits
   int32_t na;       // active particles of the cluster
   int32_t act_off;  // their offset in the active list
@@ -80,6 +87,8 @@ struct Tuning {     // device copy of the launch policy (passed by value)
   int32_t target_items[kBuckets];
   int32_t min_split_j;
   int32_t K;        // i-particles per thread slot (1 or 2)
+  int32_t fp64;     // the evaluation's own kernels are FP64
+  int32_t acc;      // acceleration only (no near pairs)
   int64_t small_work;   // small mixed block steps: at most this many
                         // interactions, or kSmallStep active; < 0: none
 };

@@ -30,11 +30,12 @@
 //    FP64 kernel, and mixed block steps with few active particles run in
 //    FP64 outright;
 //  * small active sets put several lanes on one i (P i-slots x Q j-lanes,
-//    P * Q = 256) and split j over workgroups; lanes are reduced with
-//    wavefront shuffles in a fixed tree and splits by k_sum_flag in a fixed
-//    order, so every result is deterministic;
-//  * FP64 mode accumulates each tile in FP64 and folds it into a TwoSum
-//    (hi, lo) pair; mixed mode does rsqrt, r^-3 and the jerk products in
+//    P * Q = 256) and split j over workgroups; wide items (256 i-slots in the
+//    tuning) hold 256 i, or 64 whose four waves share j; lanes are reduced
+//    with wavefront shuffles, waves through LDS and splits by k_sum_flag, all
+//    in a fixed order, so every result is deterministic;
+//  * FP64 mode accumulates in FP64 and folds at most 256 terms at a time into
+//    a TwoSum (hi, lo) pair; mixed mode does rsqrt, r^-3 and the jerk products in
 //    FP32 and folds the FP32 sums of every 64 j into an FP32 TwoSum
 //    (hi, lo) pair;
 //  * the same kernels in acceleration-only modes serve the paper's
@@ -303,6 +304,7 @@ __device__ __forceinline__ void pair_fp64(const I64 &I, int iidx, const JRec64 &
 // larger.
 struct Bnd {
   float a, f1;
+  int near;      // near pairs queued (wide items, whose waves share an i)
 };
 
 // FP32 factors shared by the mixed pair terms.  The hardware rsqrt is good
@@ -538,49 +540,49 @@ template <int MODE> struct Traits {          // FP64 forces
   using Rec = JRec64;
   using Ist = I64;
   static constexpr int NC = 6;
-  static constexpr int FOLD = kTJ;           // j per compensated fold
+  static constexpr int FOLD = 4;             // tiles of kTJ j per compensated fold
 };
 template <> struct Traits<kModeMixed> {
   using T = float;
   using Rec = JRecDS;
   using Ist = IDS;
   static constexpr int NC = 6;
-  static constexpr int FOLD = 64;
+  static constexpr int FOLD = 1;
 };
 template <> struct Traits<kModeFP64Acc> {
   using T = double;
   using Rec = JRec64;
   using Ist = I64;
   static constexpr int NC = 3;
-  static constexpr int FOLD = kTJ;
+  static constexpr int FOLD = 4;
 };
 template <> struct Traits<kModeMixedAcc> {
   using T = float;
   using Rec = JRecDS;
   using Ist = IDS;
   static constexpr int NC = 3;
-  static constexpr int FOLD = 64;
+  static constexpr int FOLD = 1;
 };
 template <> struct Traits<kModeMixed64> {
   using T = float;
   using Rec = JRecV;
   using Ist = IV;
   static constexpr int NC = 6;
-  static constexpr int FOLD = 64;
+  static constexpr int FOLD = 1;
 };
 template <> struct Traits<kModeMixed64Acc> {
   using T = float;
   using Rec = JRecV;
   using Ist = IV;
   static constexpr int NC = 3;
-  static constexpr int FOLD = 64;
+  static constexpr int FOLD = 1;
 };
 template <> struct Traits<kModePot> {
   using T = double;
   using Rec = JRec64;
   using Ist = I64;
   static constexpr int NC = 1;
-  static constexpr int FOLD = kTJ;
+  static constexpr int FOLD = 4;
 };
 
 template <int MODE, int K>
@@ -639,6 +641,7 @@ __device__ __forceinline__ void pair_k(const typename Traits<MODE>::Rec &r,
 // rare FP64 work then costs the hot loop no registers.  A lane with more
 // near pairs than the queue holds marks its particle for the FP64
 // re-evaluation of the whole evaluation.
+// The four waves of a wide item count together (kNearQ between them).
 constexpr int kNearQ = 16;
 
 template <int MODE, int K>
@@ -674,51 +677,73 @@ __device__ __forceinline__ void near_push(const uint64_t (&m)[U][K], const int (
   }
 }
 
-// One LDS tile against K i-particles, folding the running tile sums into the
-// compensated (hi, lo) pairs every FOLD records.  WIDE: every lane owns its
-// i (Q = 1); otherwise lane q of a slot takes records q, q + Q, ... and
-// folds once per tile.  Near pairs go to (hi, lo) as they come, so the
-// sequence of operations on (hi, lo) is the same as in the broadcast kernel.
-template <int MODE, int K, bool WIDE, bool MASK, bool SELF>
+// The records of one lane out of an LDS tile against its K i-particles:
+// records q, q + step, ... below cnt (step 1: a wide item's wave takes one
+// block of kBlk records).
+template <int MODE, int K, bool MASK, bool SELF>
 __device__ __forceinline__ void tile_loop(
-    const typename Traits<MODE>::Rec *tile, int cnt, int q, int Q,
+    const typename Traits<MODE>::Rec *tile, int cnt, int q, int step,
     const typename Traits<MODE>::Ist (&I)[K], const int (&iidx)[K], double eps2,
-    const float (&th)[K],
-    typename Traits<MODE>::T (&t)[K][Traits<MODE>::NC],
-    typename Traits<MODE>::T (&hi)[K][Traits<MODE>::NC],
-    typename Traits<MODE>::T (&lo)[K][Traits<MODE>::NC], int (&dom)[K],
-    Bnd (&ba)[K], int (&ncnt)[K], NearQueue<MODE, K> &nq) {
-  constexpr int F = Traits<MODE>::FOLD;
-  if (WIDE) {
-    for (int j0 = 0; j0 < cnt; j0 += F) {
-      const int j1 = (j0 + F < cnt) ? j0 + F : cnt;
-      int jj = j0;
-      for (; jj + 2 <= j1; jj += 2) {
-        uint64_t nr[2][K];
-        int ji[2];
+    const float (&th)[K], typename Traits<MODE>::T (&t)[K][Traits<MODE>::NC],
+    int (&dom)[K], Bnd (&ba)[K], int (&ncnt)[K], NearQueue<MODE, K> &nq) {
+  int jj = q;
+  for (; jj + step < cnt; jj += 2 * step) {
+    uint64_t nr[2][K];
+    int ji[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          pair_k<MODE, K, MASK, SELF>(tile[jj + u], I, iidx, eps2, th, t, dom, ba, nr[u]);
-          ji[u] = tile[jj + u].idx;
+    for (int u = 0; u < 2; ++u) {
+      const typename Traits<MODE>::Rec &r = tile[jj + u * step];
+      pair_k<MODE, K, MASK, SELF>(r, I, iidx, eps2, th, t, dom, ba, nr[u]);
+      ji[u] = r.idx;
+    }
+    near_push<MODE, K, 2>(nr, ji, ncnt, nq);
+  }
+  if (jj < cnt) {
+    uint64_t nr[1][K];
+    int ji[1] = {tile[jj].idx};
+    pair_k<MODE, K, MASK, SELF>(tile[jj], I, iidx, eps2, th, t, dom, ba, nr[0]);
+    near_push<MODE, K, 1>(nr, ji, ncnt, nq);
+  }
+}
+
+// Sums of the waves that share an item's i-slots (nwq of them, this one the
+// wq-th; `col` is the lane's slot, ncol the slots) through LDS: complete in
+// the wave with wq = 0, in a fixed order.  on: the lane holds a slot's sum.
+// red: kRedBytes of LDS, free on entry.  Called by the whole workgroup.
+constexpr int kRedCols = 192;                       // 3 waves x 64 or 1 x 128
+constexpr int kRedBytes = kRedCols * (6 * 8 + sizeof(Bnd));
+template <int NC, int K>
+__device__ __forceinline__ void combine_waves(double (&res)[K][NC], Bnd (&ba)[K], int wq, int nwq,
+                                              int col, int ncol, bool on, double *red) {
+  Bnd *redb = reinterpret_cast<Bnd *>(red + NC * kRedCols);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (k > 0) __syncthreads();
+    if (wq > 0 && on) {
+      const int e = (wq - 1) * ncol + col;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) red[c * kRedCols + e] = res[k][c];
+      redb[e] = ba[k];
+    }
+    __syncthreads();
+    if (wq == 0 && on) {
+      if (nwq == 4) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const double *r = red + c * kRedCols + col;
+          res[k][c] = (res[k][c] + r[0]) + (r[ncol] + r[2 * ncol]);
         }
-        near_push<MODE, K, 2>(nr, ji, ncnt, nq);
+        const Bnd b1 = redb[col], b2 = redb[col + ncol], b3 = redb[col + 2 * ncol];
+        ba[k].a = fmaxf(fmaxf(ba[k].a, b1.a), fmaxf(b2.a, b3.a));
+        ba[k].f1 = (ba[k].f1 + b1.f1) + (b2.f1 + b3.f1);
+        ba[k].near += b1.near + b2.near + b3.near;
+      } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) res[k][c] += red[c * kRedCols + col];
+        ba[k].a = fmaxf(ba[k].a, redb[col].a);
+        ba[k].f1 += redb[col].f1;
       }
-      if (jj < j1) {
-        uint64_t nr[1][K];
-        int ji[1] = {tile[jj].idx};
-        pair_k<MODE, K, MASK, SELF>(tile[jj], I, iidx, eps2, th, t, dom, ba, nr[0]);
-        near_push<MODE, K, 1>(nr, ji, ncnt, nq);
-      }
-      fold<MODE, K>(t, hi, lo);
     }
-  } else {
-    for (int jj = q; jj < cnt; jj += Q) {
-      uint64_t nr[1][K];
-      int ji[1] = {tile[jj].idx};
-      pair_k<MODE, K, MASK, SELF>(tile[jj], I, iidx, eps2, th, t, dom, ba, nr[0]);
-      near_push<MODE, K, 1>(nr, ji, ncnt, nq);
-    }
-    fold<MODE, K>(t, hi, lo);
   }
 }
 
@@ -832,14 +857,6 @@ __device__ __forceinline__ void rec_to_i(const JRecV &r, IV &s) {
 
 // ------------------------------------------------------------ force kernel
 
-// Waves per SIMD to aim for: the compiler's choice (1 = no minimum) for
-// every shape of this kernel; a hint of five waves on the record-only
-// double-single kernel spills its i-state since the velocity carries a low
-// part.
-template <int MODE, int SRC, int K> struct ForceOcc {
-  static constexpr int waves = 1;
-};
-
 // Per-cluster prefix arrays (work items, row-sum waves) in LDS: with several
 // clusters every work item or wave finds its cluster by a binary search,
 // which in LDS costs a few LDS reads instead of a chain of dependent global
@@ -869,19 +886,18 @@ inline size_t prefix_lds_bytes(int C) {
 }
 
 template <int MODE, int SRC, int K>
-__global__ __launch_bounds__(kWG)
-__attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force(ForceArgs A) {
+__global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
   using Tr = Traits<MODE>;
   using T = typename Tr::T;
   using Rec = typename Tr::Rec;
   constexpr int NC = Tr::NC;
   __shared__ Rec tile[kTJ];
-  __shared__ double red[kWG / 64][K][NC];
-  __shared__ Bnd red_t[kWG / 64][K];
+  static_assert(sizeof(tile) >= kRedBytes, "the waves' sums reuse the tile");
   __shared__ NearQueue<MODE, K> nq;
   __shared__ int s_g;
   const Dev &d = A.d;
   const int tid = threadIdx.x;
+  const int lane = tid & 63, wv = tid >> 6;
   // items [0, work[2]) belong to the main launches, [work[2], total) to the
   // small-step FP64 launch (clusters of a mixed block step with few active
   // particles); records built once for this evaluation (large active sets)
@@ -936,10 +952,20 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
     const int tile_i = t_item - split * cp.tiles;
     const int64_t js = cp.jb + (int64_t)split * cp.chunk;
     const int64_t je = (js + cp.chunk < cp.je) ? js + cp.chunk : cp.je;
-    const int Qlog = cp.Qlog;
-    const int Q = 1 << Qlog;
-    const int p = tid >> Qlog;
-    const int q = tid & (Q - 1);
+    // lanes of the item: i-slot p fastest, so a wave's lanes read as few
+    // different records of the tile as the slots allow (all of them one
+    // record from 64 slots on: an LDS broadcast; with the j-lanes fastest,
+    // 16 records 64 bytes apart shared 4 banks).  Wide items of kBlk slots:
+    // each wave takes its own block of kBlk records of every tile.
+    const bool wide = cp.P == kWG;
+    const int Pt = cp.Pt;
+    const int Plog = 31 - __builtin_clz(Pt);
+    const int Pwl = Plog < 6 ? Plog : 6;         // log2 of the slots in one wave
+    const int nwi = 1 << (Plog - Pwl);           // waves side by side in i
+    const int p = (lane & ((1 << Pwl) - 1)) + ((wv & (nwi - 1)) << 6);
+    const int wq = wv >> (Plog - Pwl);
+    const int q = (lane >> Pwl) + (wq << (6 - Pwl));
+    const int Q = kWG >> Plog;
     const double eps2 = d.eps2[cp.c];
     // FP32 sums in units of the cluster's reference mass (mixed modes)
     const double mref = !mode_mixed(MODE) ? 1.0
@@ -953,7 +979,7 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
     bool ok[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int slot = tile_i * cp.P * K + k * cp.P + p;
+      const int slot = tile_i * Pt * K + k * Pt + p;
       ok[k] = slot < cp.na;
       iidx[k] = ok[k] ? A.active[cp.act_off + slot] : -1;
       dom[k] = 0;
@@ -987,13 +1013,14 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
     int ncnt[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      ba[k].a = ba[k].f1 = 0.0f;
+      ba[k] = Bnd{0.0f, 0.0f, 0};
       ncnt[k] = 0;
 #pragma unroll
       for (int c = 0; c < NC; ++c) t[k][c] = shi[k][c] = slo[k][c] = (T)0;
     }
 
     const bool mask = (eps2 == 0.0);
+    int tiles = 0;
     for (int64_t jt = js; jt < je; jt += kTJ) {
       const int cnt = (int)((je - jt < kTJ) ? je - jt : kTJ);
       if (tid < cnt && use_pred) {
@@ -1025,25 +1052,32 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
       // the FP64 force terms of the i's own pair are exactly zero; the
       // mixed bound and the potential must skip it
       constexpr bool has_self = mode_mixed(MODE) || MODE == kModePot;
-      if (Q == 1) {
+      // the wave's records of this tile, in blocks: wide items take blocks of
+      // kBlk (every one, or the wave's own), others every Q-th record
+      const int q0 = wide ? 0 : q, step = wide ? 1 : Q;
+      const int b1 = !wide ? 1 : (Pt == kWG ? kTJ : (wv + 1) * kBlk);
+      for (int b0 = wide ? q * kBlk : 0; b0 < b1 && b0 < cnt; b0 += kBlk) {
+        const Rec *rb = tile + b0;
+        const int bc = (wide && cnt - b0 > kBlk) ? kBlk : cnt - b0;
         if (mask)
-          tile_loop<MODE, K, true, true, false>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
+          tile_loop<MODE, K, true, false>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
         else if (has_self && self_tile)
-          tile_loop<MODE, K, true, false, true>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
+          tile_loop<MODE, K, false, true>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
         else
-          tile_loop<MODE, K, true, false, false>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
-      } else {
-        if (mask)
-          tile_loop<MODE, K, false, true, false>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
-        else if (has_self && self_tile)
-          tile_loop<MODE, K, false, false, true>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
-        else
-          tile_loop<MODE, K, false, false, false>(tile, cnt, q, Q, I, iidx, eps2, th, t, shi, slo, dom, ba, ncnt, nq);
+          tile_loop<MODE, K, false, false>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
+        if (Tr::FOLD == 1) fold<MODE, K>(t, shi, slo);
       }
+      if (Tr::FOLD > 1 &&
+          ((++tiles & (Tr::FOLD - 1)) == 0 || Pt == kWG || jt + kTJ >= je))
+        fold<MODE, K>(t, shi, slo);
       __syncthreads();
     }
 
     near_drain<MODE, K>(A, cp, SRC == kSrcRaw, mref, iidx, ok, ncnt, nq, eps2, shi, slo, ba);
+    if constexpr (mode_near(MODE)) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) ba[k].near = wide ? ncnt[k] : 0;
+    }
     // combine hi + lo in FP64, reduce the Q lanes of a slot in a fixed tree
     double res[K][NC];
 #pragma unroll
@@ -1052,53 +1086,22 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
       for (int c = 0; c < NC; ++c) res[k][c] = ((double)shi[k][c] + (double)slo[k][c]) * mref;
       if (ok[k] && dom[k]) atomicOr(d.err, (int)kErrDomain);
     }
-    if (Q > 1) {
-      const int qw = Q < 64 ? Q : 64;
-      for (int off = 1; off < qw; off <<= 1) {
+    for (int off = 1 << Pwl; off < 64; off <<= 1) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
+      for (int k = 0; k < K; ++k) {
 #pragma unroll
-          for (int c = 0; c < NC; ++c) res[k][c] += __shfl_xor(res[k][c], off);
-          ba[k].a = fmaxf(ba[k].a, __shfl_xor(ba[k].a, off));
-          ba[k].f1 += __shfl_xor(ba[k].f1, off);
-        }
-      }
-      if (Q > 64) {
-        const int w = tid >> 6;
-        if ((tid & 63) == 0) {
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) red[w][k][c] = res[k][c];
-            red_t[w][k] = ba[k];
-          }
-        }
-        __syncthreads();
-        if (q == 0) {
-          const int nw = Q >> 6;   // waves of this slot: w .. w + nw - 1
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-              double s = red[w][k][c];
-              for (int u = 1; u < nw; ++u) s += red[w + u][k][c];
-              res[k][c] = s;
-            }
-            Bnd tm = red_t[w][k];
-            for (int u = 1; u < nw; ++u) {
-              tm.a = fmaxf(tm.a, red_t[w + u][k].a);
-              tm.f1 += red_t[w + u][k].f1;
-            }
-            ba[k] = tm;
-          }
-        }
-        __syncthreads();
+        for (int c = 0; c < NC; ++c) res[k][c] += __shfl_xor(res[k][c], off);
+        ba[k].a = fmaxf(ba[k].a, __shfl_xor(ba[k].a, off));
+        ba[k].f1 += __shfl_xor(ba[k].f1, off);
       }
     }
+    if (Pt != kWG)
+      combine_waves<NC, K>(res, ba, wq, (kWG / 64) / nwi, p, Pt, (lane >> Pwl) == 0,
+                           reinterpret_cast<double *>(tile));
     if (q == 0) {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const int slot = tile_i * cp.P * K + k * cp.P + p;
+        const int slot = tile_i * Pt * K + k * Pt + p;
         if (slot < cp.na) {
           double *row = d.partial + (cp.row_off + (int64_t)split * cp.na + slot) * kRowStride;
 #pragma unroll
@@ -1106,6 +1109,7 @@ __attribute__((amdgpu_waves_per_eu(ForceOcc<MODE, SRC, K>::waves))) void k_force
           if (MODE != kModePot) {
 #pragma unroll
             for (int c = NC; c < 6; ++c) row[c] = 0.0;    // no jerk in acc-only modes
+            if (ba[k].near > kNearQ) ba[k].a = INFINITY;
             row[6] = ok[k] ? (double)ba[k].a * mref : 0.0;
             row[7] = ok[k] ? (double)ba[k].f1 * mref : 0.0;
           }
@@ -1265,7 +1269,7 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
   ClusterPlan p;
   p.c = c;
   p.P = 256;
-  p.Qlog = 0;
+  p.Pt = 256;
   p.S = 0;
   p.na = na;
   p.act_off = act_off;
@@ -1292,12 +1296,19 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     if (P > 256) P = 256;
     P = 1 << (31 - __builtin_clz((unsigned)P));      // power of two
     p.P = P;
-    p.Qlog = 8 - (31 - __builtin_clz((unsigned)P));
     const int64_t ipt = (int64_t)P * K;
-    const int64_t tiles = (p.na + ipt - 1) / ipt;
+    int64_t tiles = (p.na + ipt - 1) / ipt;
     int64_t target = tu.target_items[b] > 0 ? tu.target_items[b] : 1;
     int64_t S = (target + tiles - 1) / tiles;
-    const int64_t mj = tu.min_split_j > 0 ? tu.min_split_j : 64;
+    p.small = (allow_small && kind == kPlanStep && tu.small_work >= 0 &&
+               (p.na <= kSmallStep || (int64_t)p.na * nc <= tu.small_work)) ? 1 : 0;
+    const bool fp64 = tu.fp64 || p.small || kind == kPlanRefine || kind == kPlanApiRefine;
+    int64_t mj = tu.min_split_j > 0 ? tu.min_split_j : 64;
+    // wide items whose rows may be cut anywhere (the FP32 forms with jerk
+    // count an item's near pairs): 4 kTJ records at least, which lets their
+    // waves share j (below), where that leaves items for half the CUs
+    if (P == kWG && (fp64 || tu.acc) && mj < 4 * kTJ && tiles * nc >= kFewItems / 2 * 4 * kTJ)
+      mj = 4 * kTJ;
     const int64_t s_j = (nc + mj - 1) / mj;
     if (S > s_j) S = s_j;
     // partial rows of a cluster: at most kRowsPerJ per j-particle (so an
@@ -1313,13 +1324,26 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     S = (nc + chunk - 1) / chunk;
     p.S = (int32_t)S;
     p.chunk = chunk;
+    // Wide items (P = kWG) in one of two shapes with the same j-splits and
+    // rows: kWG i-slots whose four waves meet the same records, or kBlk
+    // slots whose four waves share the records between them.  The second
+    // cuts the i-tiles' rounding and the idle tail of the last items to a
+    // quarter (FP64-difference mixed, all of 2^16 in 8192 items on 1280
+    // workgroups: 6.77 -> 6.60 ms a two-pass evaluation; 20000 of 2^18:
+    // 8.54 -> 8.01 ms), but reads each record four times as often through
+    // the scalar cache and pays an item's start and end on a quarter of the
+    // pairs: with 256-record chunks all of 2^14 took 703 us against 568, and
+    // all of 2^20 (131072 items) 1554 ms against 1548.  So it needs chunks of
+    // 4 kTJ, or too few items to fill the chip (N = 1000: 170 -> 99 us), and
+    // is left where the items are many anyway.
+    p.Pt = (P == kWG && tiles * S < kWideItems && (chunk >= 4 * kTJ || tiles * S < kFewItems))
+               ? kBlk : P;
+    if (p.Pt != P) tiles = (p.na + (int64_t)kBlk * K - 1) / ((int64_t)kBlk * K);
     p.tiles = (int32_t)tiles;
     p.items = (int32_t)(tiles * S);
     int g = 0;
     while (g < 6 && (1 << g) < S) ++g;
     p.glog = g;
-    p.small = (allow_small && kind == kPlanStep && tu.small_work >= 0 &&
-               (p.na <= kSmallStep || (int64_t)p.na * nc <= tu.small_work)) ? 1 : 0;
   }
   return p;
 }
@@ -1724,6 +1748,7 @@ __global__ __launch_bounds__(BS) void k_plan(Dev d, Tuning tu, int kind,
       p = ClusterPlan{};
       p.c = c;
       p.P = 256;
+      p.Pt = 256;
       p.chunk = kTJ;
       continue;
     }
@@ -1752,7 +1777,7 @@ __global__ __launch_bounds__(BS) void k_plan(Dev d, Tuning tu, int kind,
     if (kind == kPlanStep && d.Tnext[c] < d.ctr[kCtrTend]) ++my_notdone;
     // main-kernel clusters first, then small-step ones; within each, largest
     // item cost first, ties by cluster id (keys are unique)
-    const uint64_t cost = p.items > 0 ? (uint64_t)p.P * K * p.chunk : 0;   // < 2^40
+    const uint64_t cost = p.items > 0 ? (uint64_t)p.Pt * K * p.chunk : 0;   // < 2^40
     key[c] = ((uint64_t)p.small << 63) | ((((uint64_t)1 << 40) - 1 - cost) << 12) |
              (uint64_t)c;
   }
@@ -2219,24 +2244,35 @@ __global__ __launch_bounds__(kWG) void k_records(Dev d, int kind, RawSrc raw, in
 template <typename T>
 using ScalarPtr = const __attribute__((address_space(4))) T *;
 
-// member-wise copies (the implicit copy constructor takes a generic pointer)
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
 __device__ __forceinline__ JRecDS load_rec(ScalarPtr<JRecDS> p) {
+  const f32x16 a = *(ScalarPtr<f32x16>)p;    // one request for the record
   JRecDS r;
-  r.xh = p->xh; r.yh = p->yh; r.zh = p->zh; r.m = p->m;
-  r.xl = p->xl; r.yl = p->yl; r.zl = p->zl; r.pad0 = 0.0f;
-  r.vx = p->vx; r.vy = p->vy; r.vz = p->vz; r.idx = p->idx;
-  r.vlx = p->vlx; r.vly = p->vly; r.vlz = p->vlz; r.pad1 = 0.0f;
+  r.xh = a[0]; r.yh = a[1]; r.zh = a[2]; r.m = a[3];
+  r.xl = a[4]; r.yl = a[5]; r.zl = a[6]; r.pad0 = 0.0f;
+  r.vx = a[8]; r.vy = a[9]; r.vz = a[10];
+  r.idx = __float_as_int(a[11]);
+  r.vlx = a[12]; r.vly = a[13]; r.vlz = a[14]; r.pad1 = 0.0f;
   return r;
 }
 
 __device__ __forceinline__ JRec64 load_rec(ScalarPtr<JRec64> p) {
+  const f32x16 a = *(ScalarPtr<f32x16>)p;    // one request for the record
   JRec64 r;
-  r.x = p->x; r.y = p->y; r.z = p->z; r.m = p->m;
-  r.vx = p->vx; r.vy = p->vy; r.vz = p->vz;
-  r.mf = p->mf; r.idx = p->idx;
+  r.x = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 0, 1));
+  r.y = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 2, 3));
+  r.z = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 4, 5));
+  r.m = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 6, 7));
+  r.vx = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 8, 9));
+  r.vy = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 10, 11));
+  r.vz = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 12, 13));
+  r.mf = a[14];
+  r.idx = __float_as_int(a[15]);
   return r;
 }
 
+// member-wise (a j-particle needs 11 of the 16 dwords)
 __device__ __forceinline__ JRecV load_rec(ScalarPtr<JRecV> p) {
   JRecV r;
   r.x = p->x; r.y = p->y; r.z = p->z;
@@ -2247,59 +2283,11 @@ __device__ __forceinline__ JRecV load_rec(ScalarPtr<JRecV> p) {
   return r;
 }
 
-// Four records per group, read with as few scalar loads as possible (a
-// 64-byte load is one request to the scalar cache).
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-// one 64-byte block per record
-__device__ __forceinline__ void load4(ScalarPtr<JRecDS> p, JRecDS (&r)[4]) {
-  const ScalarPtr<f32x16> b = (ScalarPtr<f32x16>)p;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const f32x16 a = b[u];
-    r[u].xh = a[0]; r[u].yh = a[1]; r[u].zh = a[2]; r[u].m = a[3];
-    r[u].xl = a[4]; r[u].yl = a[5]; r[u].zl = a[6]; r[u].pad0 = 0.0f;
-    r[u].vx = a[8]; r[u].vy = a[9]; r[u].vz = a[10];
-    r[u].idx = __float_as_int(a[11]);
-    r[u].vlx = a[12]; r[u].vly = a[13]; r[u].vlz = a[14]; r[u].pad1 = 0.0f;
-  }
-}
-
-__device__ __forceinline__ void load4(ScalarPtr<JRec64> p, JRec64 (&r)[4]) {
-  const ScalarPtr<f32x16> b = (ScalarPtr<f32x16>)p;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const f32x16 a = b[u];
-    r[u].x = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 0, 1));
-    r[u].y = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 2, 3));
-    r[u].z = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 4, 5));
-    r[u].m = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 6, 7));
-    r[u].vx = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 8, 9));
-    r[u].vy = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 10, 11));
-    r[u].vz = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 12, 13));
-    r[u].mf = a[14];
-    r[u].idx = __float_as_int(a[15]);
-  }
-}
-
-__device__ __forceinline__ void load4(ScalarPtr<JRecV> p, JRecV (&r)[4]) {
-  const ScalarPtr<f32x16> b = (ScalarPtr<f32x16>)p;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const f32x16 a = b[u];
-    r[u].x = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 0, 1));
-    r[u].y = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 2, 3));
-    r[u].z = __builtin_bit_cast(double, __builtin_shufflevector(a, a, 4, 5));
-    r[u].vx = a[6]; r[u].vy = a[7]; r[u].vz = a[8];
-    r[u].mf = a[9];
-    r[u].idx = __float_as_int(a[10]);
-    r[u].vlx = a[11]; r[u].vly = a[12]; r[u].vlz = a[13];
-    r[u].pad[0] = r[u].pad[1] = 0;
-  }
-}
-
-// A chunk of records against the lane's K i-particles, four records per
-// scalar load group; near pairs go to the lane's queue.
+// cnt records against the lane's K i-particles, G records per scalar load
+// group; near pairs go to the lane's queue.  Each group's first
+// record is loaded one group early, so the group starts without waiting on
+// the scalar cache (FP64, 4885 of 65536 particles: 490 -> 430 us); the
+// prefetch address stays inside the block.
 template <int MODE, int K, bool MASK, bool SELF>
 __device__ __forceinline__ void sb_run(
     ScalarPtr<typename Traits<MODE>::Rec> rec, int cnt,
@@ -2307,44 +2295,39 @@ __device__ __forceinline__ void sb_run(
     const float (&th)[K], typename Traits<MODE>::T (&t)[K][Traits<MODE>::NC],
     int (&dom)[K], Bnd (&ba)[K], int (&ncnt)[K], NearQueue<MODE, K> &nq) {
   using Rec = typename Traits<MODE>::Rec;
+  // FP64: four records and the early one leave too few scalar registers for
+  // the rest (spills to vector lanes: 4 instructions a pair)
+  constexpr int G = MODE == kModeFP64 ? 3 : 4;
+  // Keep the order written here: all loads of the group, then one record
+  // after the other.  Left alone, the scheduler sinks loads to just before
+  // their use and waits three times a group instead of once (mixed, all of
+  // 2^16: 6.89 -> 6.44 ms a two-pass call; acceleration only 1.85 -> 1.78;
+  // FP64 417 -> 398 us at 5000 of 65536).  The double-single loop, whose
+  // scheduler does neither, runs out of vector registers that way (7.60 ->
+  // 8.70 ms).
+  constexpr bool fence = MODE != kModeMixed;
   int jj = 0;
-  if constexpr (mode_relv(MODE) && !mode_acc_only(MODE)) {
-    // JRecV (11 of its 16 dwords read for a j-particle): each group's first record is loaded
-    // one group early, so the group starts without waiting on the scalar
-    // cache; the prefetch address stays inside the chunk
-    Rec first = load_rec(rec + 0);
-    for (; jj + 4 <= cnt; jj += 4) {
-      Rec r[4];
-      uint64_t nr[4][K];
-      int ji[4];
-      r[0] = first;
-      r[1] = load_rec(rec + jj + 1);
-      r[2] = load_rec(rec + jj + 2);
-      r[3] = load_rec(rec + jj + 3);
-      first = load_rec(rec + ((jj + 4 < cnt) ? jj + 4 : cnt - 1));
+  Rec first = load_rec(rec);
+  for (; jj + G <= cnt; jj += G) {
+    Rec r[G];
+    uint64_t nr[G][K];
+    int ji[G];
+    r[0] = first;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        pair_k<MODE, K, MASK, SELF>(r[u], I, iidx, eps2, th, t, dom, ba, nr[u]);
-        ji[u] = r[u].idx;
-      }
-      near_push<MODE, K, 4>(nr, ji, ncnt, nq);
-    }
-  } else {
-    for (; jj + 4 <= cnt; jj += 4) {
-      Rec r[4];
-      uint64_t nr[4][K];
-      int ji[4];
-      load4(rec + jj, r);
+    for (int u = 1; u < G; ++u) r[u] = load_rec(rec + u);
+    if (jj + G < cnt) rec += G;
+    first = load_rec(rec);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        pair_k<MODE, K, MASK, SELF>(r[u], I, iidx, eps2, th, t, dom, ba, nr[u]);
-        ji[u] = r[u].idx;
-      }
-      near_push<MODE, K, 4>(nr, ji, ncnt, nq);
+    for (int u = 0; u < G; ++u) {
+      if constexpr (fence) __builtin_amdgcn_sched_barrier(0);
+      pair_k<MODE, K, MASK, SELF>(r[u], I, iidx, eps2, th, t, dom, ba, nr[u]);
+      ji[u] = r[u].idx;
     }
+    near_push<MODE, K, G>(nr, ji, ncnt, nq);
   }
-  for (; jj < cnt; ++jj) {
-    const Rec r = load_rec(rec + jj);
+  for (; jj < cnt; ++jj) {             // `first` is record jj here
+    const Rec r = first;
+    if (jj + 1 < cnt) first = load_rec(++rec);
     uint64_t nr[1][K];
     int ji[1] = {r.idx};
     pair_k<MODE, K, MASK, SELF>(r, I, iidx, eps2, th, t, dom, ba, nr[0]);
@@ -2352,10 +2335,16 @@ __device__ __forceinline__ void sb_run(
   }
 }
 
-// The mixed broadcast kernel with one i per lane holds five waves per SIMD
-// (at most 96 VGPRs); the others keep the compiler's choice.
+// Waves per SIMD the broadcast kernel is held to (1: the compiler's choice).
+// The mixed forms with one i per lane: five (96 VGPRs).  Six (80, spilling
+// around the pair loop) took 97.3 against 97.7 ms at 2^18 but 562 against
+// 538 us at 2^14, whose items are short; double-single with four: 8.42
+// against 7.60 ms at 2^16.
 template <int MODE, int K> struct SbOcc {
-  static constexpr int waves = (mode_near(MODE) && K == 1) ? 5 : 1;
+  static constexpr int waves = (mode_near(MODE) && K == 1)       ? 5
+                               : (MODE == kModeFP64 && K == 2)    ? 3
+                               : (MODE == kModeFP64Acc)           ? 5
+                                                                  : 1;
 };
 
 template <int MODE, int K>
@@ -2365,12 +2354,19 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
   using T = typename Tr::T;
   using Rec = typename Tr::Rec;
   constexpr int NC = Tr::NC;
-  constexpr int F = Tr::FOLD;
   __shared__ int s_g;
-  __shared__ NearQueue<MODE, K> nq;
+  // the near-pair queues of an item and, once they are drained, the waves'
+  // sums share one piece of LDS (six workgroups then fit a CU)
+  __shared__ union {
+    NearQueue<MODE, K> nq;
+    double red[kRedBytes / 8];
+  } lds;
+  NearQueue<MODE, K> &nq = lds.nq;
   const Dev &d = A.d;
   if (*A.pred_on != 2) return;      // the workgroup kernel takes this evaluation
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_items = d.work[2];    // the main items
   if (n_items <= 0) return;
   const Rec *pred = reinterpret_cast<const Rec *>(d.pred);
@@ -2403,6 +2399,13 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
     const double mref = !mode_mixed(MODE) ? 1.0 : mass_ref(raw ? A.rm[cp.jb] : d.m[cp.jb]);
     double vref[3];
     ref_velocity<MODE>(A, cp, raw, vref);
+    // kWG slots, every wave all blocks of kBlk records (`turn` apart), or
+    // kBlk slots, each wave every fourth block
+    const int Pt = cp.Pt;
+    const bool all_j = Pt == kWG;
+    const int my_slot = all_j ? tid : lane;
+    const int turn = all_j ? kBlk : kTJ;
+    const int first_j = all_j ? 0 : wv * kBlk;
 
     typename Tr::Ist I[K];
     int iidx[K], dom[K];
@@ -2410,13 +2413,13 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
     bool ok[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int slot = tile_i * kWG * K + k * kWG + tid;
+      const int slot = tile_i * Pt * K + k * Pt + my_slot;
       ok[k] = slot < cp.na;
       iidx[k] = ok[k] ? A.active[cp.act_off + slot] : -1;
       dom[k] = 0;
       if (raw && ok[k] && (iidx[k] < cp.jb || iidx[k] >= cp.je)) {
         ok[k] = false;
-        if (split == 0) atomicOr(d.err, (int)kErrIndex);
+        if (split == 0 && first_j == 0) atomicOr(d.err, (int)kErrIndex);
       }
       // the FP32 jerk scales are in units of mref
       th[k] = (mode_near(MODE) && ok[k])
@@ -2435,19 +2438,22 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
     int ncnt[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      ba[k].a = ba[k].f1 = 0.0f;
+      ba[k] = Bnd{0.0f, 0.0f, 0};
       ncnt[k] = 0;
 #pragma unroll
       for (int c = 0; c < NC; ++c) t[k][c] = shi[k][c] = slo[k][c] = (T)0;
     }
 
     const bool mask = (eps2 == 0.0);
-    for (int64_t jb = js; jb < je; jb += F) {
-      const int cnt = (int)((je - jb < F) ? je - jb : F);
+    // the block of records that starts at jb
+    auto block = [&](int64_t jb) {
+      const int64_t left = je - jb;
+      if (left <= 0) return;
+      const int cnt = (int)(left < kBlk ? left : kBlk);
       int mine = 0;
 #pragma unroll
       for (int k = 0; k < K; ++k) mine |= (iidx[k] >= jb && iidx[k] < jb + cnt);
-      const bool self = __any(mine);
+      const bool self = mode_mixed(MODE) && __any(mine);
       const ScalarPtr<Rec> rb = spred + jb;
       if (mask)
         sb_run<MODE, K, true, false>(rb, cnt, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
@@ -2455,23 +2461,50 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
         sb_run<MODE, K, false, true>(rb, cnt, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
       else
         sb_run<MODE, K, false, false>(rb, cnt, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
-      fold<MODE, K>(t, shi, slo);
+    };
+    if constexpr (Tr::FOLD == 1) {
+      for (int64_t jb = js + first_j; jb < je; jb += turn) {
+        block(jb);
+        fold<MODE, K>(t, shi, slo);
+      }
+    } else {
+      for (int64_t jg = js + first_j; jg < je; jg += Tr::FOLD * turn) {
+#pragma unroll 1
+        for (int u = 0; u < Tr::FOLD; ++u) block(jg + u * turn);
+        fold<MODE, K>(t, shi, slo);
+      }
     }
     near_drain<MODE, K>(A, cp, raw, mref, iidx, ok, ncnt, nq, eps2, shi, slo, ba);
+    if constexpr (mode_near(MODE)) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) ba[k].near = ncnt[k];
+    }
 
+    double res[K][NC];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) res[k][c] = ((double)shi[k][c] + (double)slo[k][c]) * mref;
       if (ok[k] && dom[k]) atomicOr(d.err, (int)kErrDomain);
-      const int slot = tile_i * kWG * K + k * kWG + tid;
-      if (slot < cp.na) {
-        double *row = d.partial + (cp.row_off + (int64_t)split * cp.na + slot) * kRowStride;
+    }
+    if (!all_j) {
+      if (mode_near(MODE)) __syncthreads();       // every wave's queue drained
+      combine_waves<NC, K>(res, ba, wv, kWG / 64, lane, kBlk, true, lds.red);
+    }
+    if (all_j || wv == 0) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-          row[c] = ok[k] ? ((double)shi[k][c] + (double)slo[k][c]) * mref : 0.0;
+      for (int k = 0; k < K; ++k) {
+        const int slot = tile_i * Pt * K + k * Pt + my_slot;
+        if (slot < cp.na) {
+          double *row = d.partial + (cp.row_off + (int64_t)split * cp.na + slot) * kRowStride;
 #pragma unroll
-        for (int c = NC; c < 6; ++c) row[c] = 0.0;
-        row[6] = ok[k] ? (double)ba[k].a * mref : 0.0;
-        row[7] = ok[k] ? (double)ba[k].f1 * mref : 0.0;
+          for (int c = 0; c < NC; ++c) row[c] = ok[k] ? res[k][c] : 0.0;
+#pragma unroll
+          for (int c = NC; c < 6; ++c) row[c] = 0.0;
+          if (ba[k].near > kNearQ) ba[k].a = INFINITY;
+          row[6] = ok[k] ? (double)ba[k].a * mref : 0.0;
+          row[7] = ok[k] ? (double)ba[k].f1 * mref : 0.0;
+        }
       }
     }
   }
