@@ -516,9 +516,9 @@ __device__ __forceinline__ void near_fp64(const I64 &I, const JRec64 &r, double 
   for (int c = 0; c < 6; ++c) near_add(tt[c], shi[c], slo[c]);
 }
 
-// Potential -m_j / sqrt(s) (energy diagnostics).  The i's own pair is
-// skipped: by s == 0 when unsoftened (MASK, as for the forces), else by
-// index in the tiles that can hold i (SELF).
+// Potential -m_j / sqrt(s) (energy diagnostics), each pair once: the terms
+// of j <= i drop out by index in the tiles that hold such j (SELF; the item
+// skips the tiles that hold nothing else).  2^18 particles: 36.0 -> 20.8 ms.
 template <bool MASK, bool SELF>
 __device__ __forceinline__ void pair_pot(const I64 &I, int iidx, const JRec64 &r,
                                          double eps2, double *t, int &dom) {
@@ -531,7 +531,7 @@ __device__ __forceinline__ void pair_pot(const I64 &I, int iidx, const JRec64 &r
       dom |= (r.idx != iidx);
     }
   }
-  if (SELF && r.idx == iidx) rinv = 0.0;
+  if (SELF && r.idx <= iidx) rinv = 0.0;
   t[0] = fma(-r.m, rinv, t[0]);
 }
 
@@ -1021,7 +1021,14 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
 
     const bool mask = (eps2 == 0.0);
     int tiles = 0;
-    for (int64_t jt = js; jt < je; jt += kTJ) {
+    int64_t jt0 = js;
+    if (MODE == kModePot) {
+      // every particle is active, in order: slot k is particle jb + k, and
+      // the tiles before the item's first i hold only pairs of other items
+      const int64_t i0 = cp.jb + (int64_t)tile_i * Pt * K;
+      if (i0 > js) jt0 = js + (i0 - js) / kTJ * kTJ;
+    }
+    for (int64_t jt = jt0; jt < je; jt += kTJ) {
       const int cnt = (int)((je - jt < kTJ) ? je - jt : kTJ);
       if (tid < cnt && use_pred) {
         tile[tid] = pred[jt + tid];
@@ -1047,7 +1054,8 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
       // the tile (a handful of tiles per item: the active list is ascending)
       int mine = 0;
 #pragma unroll
-      for (int k = 0; k < K; ++k) mine |= (iidx[k] >= jt && iidx[k] < jt + cnt);
+      for (int k = 0; k < K; ++k)
+        mine |= (iidx[k] >= jt && (MODE == kModePot || iidx[k] < jt + cnt));
       const bool self_tile = __syncthreads_or(mine) != 0;
       // the FP64 force terms of the i's own pair are exactly zero; the
       // mixed bound and the potential must skip it
@@ -1060,7 +1068,7 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
         const Rec *rb = tile + b0;
         const int bc = (wide && cnt - b0 > kBlk) ? kBlk : cnt - b0;
         if (mask)
-          tile_loop<MODE, K, true, false>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
+          tile_loop<MODE, K, true, MODE == kModePot>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
         else if (has_self && self_tile)
           tile_loop<MODE, K, false, true>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
         else
@@ -1343,6 +1351,9 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     p.items = (int32_t)(tiles * S);
     int g = 0;
     while (g < 6 && (1 << g) < S) ++g;
+    // beyond 2^17 lanes fewer of them per entry: the sums are then bound by
+    // memory, and the corrector after them runs on more of a wave's lanes
+    while (g > 0 && ((int64_t)p.na << g) > ((int64_t)1 << 17)) --g;
     p.glog = g;
   }
   return p;
@@ -1944,11 +1955,43 @@ __device__ double ext_pot(const Field &f, const double x[3]) {
   return p;
 }
 
+// Level changes of one block's corrections: those of cluster c gather in LDS
+// and reach the histogram once per block and level: two same-address atomics
+// per particle, 5.7 ns each, were most of k_ref_final at 2^18 particles due
+// (750 us; the launch's mean over a block-step run 8.9 -> 6.6 us) and of
+// k_sum_correct at 2^16 (298 us; mean 12.7 -> 10.6 us, with the smaller
+// row-sum groups of plan_cluster).  Set up and flushed by the whole block.
+struct LevelCounts {
+  int *n;       // LDS, kLevels
+  int c;
+  __device__ void begin(int *lds, int cluster) {
+    n = lds;
+    c = cluster;
+    if (threadIdx.x < kLevels) n[threadIdx.x] = 0;
+    __syncthreads();
+  }
+  __device__ void change(const Dev &d, int cluster, int from, int to) const {
+    if (cluster == c) {
+      atomicSub(&n[from], 1);
+      atomicAdd(&n[to], 1);
+    } else {
+      atomicSub(&d.hist[cluster * kLevels + from], 1);
+      atomicAdd(&d.hist[cluster * kLevels + to], 1);
+    }
+  }
+  __device__ void flush(const Dev &d) const {
+    __syncthreads();
+    if (threadIdx.x < kLevels && n[threadIdx.x])
+      atomicAdd(&d.hist[c * kLevels + threadIdx.x], n[threadIdx.x]);
+  }
+};
+
 // Hermite-4 correction of active particle i (cluster c) with its new force
 // f (pair sums: a, jerk), new level, bookkeeping.
 template <bool FIELD>
 __device__ __forceinline__ void correct_one(const Dev &d, int64_t i, int c, double (&f)[6],
-                                            double eta, double dt_shared, int lmin, int lmax) {
+                                            double eta, double dt_shared, int lmin, int lmax,
+                                            const LevelCounts &lc) {
   const int64_t n = d.n;
   const int64_t tn = d.Tnext[c];
   const double h = (double)(tn - d.tick[i]) * kTick;
@@ -1999,8 +2042,7 @@ __device__ __forceinline__ void correct_one(const Dev &d, int64_t i, int c, doub
     const int nl = next_level(lv, dtc, tn, lmin, lmax, fl);
     if (fl) atomicAdd((unsigned long long *)&d.ctr[kCtrFloor], 1ull);
     if (nl != lv) {
-      atomicSub(&d.hist[c * kLevels + lv], 1);
-      atomicAdd(&d.hist[c * kLevels + nl], 1);
+      lc.change(d, c, lv, nl);
       d.level[i] = nl;
     }
   }
@@ -2023,6 +2065,11 @@ __global__ __launch_bounds__(kWG) void k_sum_correct(Dev d, double eta, double d
     prefix_to_lds(d.sum_prefix, d.C, s_spre);
   }
   const int32_t *spre = lds_pre ? s_spre : d.sum_prefix;
+  const int first = wave0 - (int)(threadIdx.x >> 6);     // the block's first wave
+  if (first >= nw) return;
+  __shared__ int lh[kLevels];
+  LevelCounts lc;
+  lc.begin(lh, (d.C > 1) ? prefix_find(spre, d.C, first) : 0);
   for (int w = wave0; w < nw; w += nwaves) {
     // largest c with sum_prefix[c] <= w
     const int c = (d.C > 1) ? prefix_find(spre, d.C, w) : 0;
@@ -2033,8 +2080,9 @@ __global__ __launch_bounds__(kWG) void k_sum_correct(Dev d, double eta, double d
     group_sum_rows(d, cp, slot, cp.glog, valid, f, tmax, tf1);
     if (!valid || (lane & ((1 << cp.glog) - 1)) != 0) continue;
     const int64_t k = cp.act_off + slot;
-    correct_one<FIELD>(d, d.active[k], c, f, eta, dt_shared, lmin, lmax);
+    correct_one<FIELD>(d, d.active[k], c, f, eta, dt_shared, lmin, lmax, lc);
   }
+  lc.flush(d);
 }
 
 // After the initial force evaluation: store a, jerk, choose levels, build
@@ -2768,18 +2816,24 @@ __global__ __launch_bounds__(kWG) void k_rscatter(Dev d, const int32_t *list,
 // from the state) has finished.
 template <bool CORR, bool FIELD>
 __global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, CorrectSpec cs) {
+  __shared__ int lh[kLevels];
+  LevelCounts lc{lh, -1};
   if constexpr (CORR) {
     if ((int)blockIdx.x >= ref_blocks) {
       const int na = d.act_off[d.C];
       const int stride = ((int)gridDim.x - ref_blocks) * kWG;
+      const int k0 = ((int)blockIdx.x - ref_blocks) * kWG;
+      if (k0 >= na) return;
+      lc.begin(lh, d.cid[d.active[k0]]);
       for (int k = ((int)blockIdx.x - ref_blocks) * kWG + threadIdx.x; k < na; k += stride) {
         if (d.rflag[k]) continue;           // corrected by its wave below
         const int64_t i = d.active[k];
         double f[6];
 #pragma unroll
         for (int q = 0; q < 6; ++q) f[q] = d.fsum[6 * (int64_t)k + q];
-        correct_one<FIELD>(d, i, d.cid[i], f, cs.eta, cs.dt_shared, cs.lmin, cs.lmax);
+        correct_one<FIELD>(d, i, d.cid[i], f, cs.eta, cs.dt_shared, cs.lmin, cs.lmax, lc);
       }
+      lc.flush(d);
       return;
     }
   }
@@ -2804,68 +2858,111 @@ __global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, Correc
 #pragma unroll
       for (int q = 0; q < 6; ++q) d.fsum[6 * k + q] = f[q];
       if constexpr (CORR)
-        correct_one<FIELD>(d, d.ref_i[r], c, f, cs.eta, cs.dt_shared, cs.lmin, cs.lmax);
+        // (a few entries a step: straight to the histogram, lc holds no cluster)
+        correct_one<FIELD>(d, d.ref_i[r], c, f, cs.eta, cs.dt_shared, cs.lmin, cs.lmax, lc);
     }
   }
 }
 
-// Per-cluster diagnostics: one workgroup per cluster, fixed-order sums.
+// Per-cluster diagnostics in fixed-order compensated sums, `parts` workgroups
+// per cluster (blockIdx.y), whose sums k_energy_final adds; with one part the
+// workgroup finishes the cluster itself.  (One workgroup per cluster, the last
+// 512 terms of each sum added by one thread, took 152 us at N = 1024 and
+// 1.9 ms at 2^18; now 15 and 37 us.)
+__device__ __forceinline__ void energy_out(const Dev &d, int c, const double *t) {
+  double *o = d.eout + 9 * (int64_t)c;
+  o[0] = t[0];
+  o[1] = t[1];
+  o[2] = t[0] + t[1] + t[8];
+  for (int q = 0; q < 6; ++q) o[3 + q] = t[2 + q];
+}
+
+// The block's sums of the threads' (s, c) pairs, complete in thread 0.
+__device__ __forceinline__ void energy_block(double (&s)[9], double (&c)[9], double (*sh)[18]) {
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    for (int off = 1; off < 64; off <<= 1) {
+      const double os = __shfl_down(s[q], off), oc = __shfl_down(c[q], off);
+      c[q] += oc;
+      neu_add(s[q], c[q], os);
+    }
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+    for (int q = 0; q < 9; ++q) {
+      sh[w][2 * q] = s[q];
+      sh[w][2 * q + 1] = c[q];
+    }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int u = 1; u < kWG / 64; ++u)
+      for (int q = 0; q < 9; ++q) {
+        c[q] += sh[u][2 * q + 1];
+        neu_add(s[q], c[q], sh[u][2 * q]);
+      }
+}
+
 template <bool FIELD>
-__global__ __launch_bounds__(kWG) void k_energy_reduce(Dev d) {
-  __shared__ double sh[kWG][2];
-  const int c = blockIdx.x;
+__global__ __launch_bounds__(kWG) void k_energy_reduce(Dev d, double *part) {
+  __shared__ double sh[kWG / 64][18];
+  const int c = blockIdx.x, parts = gridDim.y;
   const ClusterPlan cp = d.plan_c[c];
   const int64_t b = d.coff[c], e = d.coff[c + 1];
   const int64_t T = d.T[c];
   // quantities: K, W, Lx, Ly, Lz, Px, Py, Pz, external potential energy
   double s[9], cc[9];
+#pragma unroll
   for (int q = 0; q < 9; ++q) s[q] = cc[q] = 0.0;
-  auto add = [&](int q, double x) {
-    const double u = s[q] + x;
-    cc[q] += (fabs(s[q]) >= fabs(x)) ? (s[q] - u) + x : (x - u) + s[q];
-    s[q] = u;
-  };
-  for (int64_t i = b + threadIdx.x; i < e; i += kWG) {
+  for (int64_t i = b + (int64_t)blockIdx.y * kWG + threadIdx.x; i < e;
+       i += (int64_t)parts * kWG) {
     double xp[3], vp[3];
     predict_state(d, i, T, xp, vp);
     const double m = d.m[i];
-    double phi;
+    double phi;                   // over the pairs with j > i
     sum_rows(d, cp, (int)(i - cp.act_off), 1, &phi);
-    add(0, 0.5 * m * (vp[0] * vp[0] + vp[1] * vp[1] + vp[2] * vp[2]));
-    add(1, 0.5 * m * phi);
-    add(2, m * (xp[1] * vp[2] - xp[2] * vp[1]));
-    add(3, m * (xp[2] * vp[0] - xp[0] * vp[2]));
-    add(4, m * (xp[0] * vp[1] - xp[1] * vp[0]));
-    add(5, m * vp[0]);
-    add(6, m * vp[1]);
-    add(7, m * vp[2]);
-    if (FIELD) add(8, m * ext_pot(d.fld, xp));
+    neu_add(s[0], cc[0], 0.5 * m * (vp[0] * vp[0] + vp[1] * vp[1] + vp[2] * vp[2]));
+    neu_add(s[1], cc[1], m * phi);
+    neu_add(s[2], cc[2], m * (xp[1] * vp[2] - xp[2] * vp[1]));
+    neu_add(s[3], cc[3], m * (xp[2] * vp[0] - xp[0] * vp[2]));
+    neu_add(s[4], cc[4], m * (xp[0] * vp[1] - xp[1] * vp[0]));
+    neu_add(s[5], cc[5], m * vp[0]);
+    neu_add(s[6], cc[6], m * vp[1]);
+    neu_add(s[7], cc[7], m * vp[2]);
+    if (FIELD) neu_add(s[8], cc[8], m * ext_pot(d.fld, xp));
   }
-  double out[9];
-  for (int q = 0; q < 9; ++q) {
-    sh[threadIdx.x][0] = s[q];
-    sh[threadIdx.x][1] = cc[q];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double S = 0.0, Cc = 0.0;
-      for (int u = 0; u < kWG; ++u) {
-        for (int h = 0; h < 2; ++h) {
-          const double x = sh[u][h];
-          const double t = S + x;
-          Cc += (fabs(S) >= fabs(x)) ? (S - t) + x : (x - t) + S;
-          S = t;
-        }
-      }
-      out[q] = S + Cc;
+  energy_block(s, cc, sh);
+  if (threadIdx.x != 0) return;
+  if (parts == 1) {
+    double t[9];
+    for (int q = 0; q < 9; ++q) t[q] = s[q] + cc[q];
+    energy_out(d, c, t);
+  } else {
+    double *p = part + 18 * ((int64_t)c * parts + blockIdx.y);
+    for (int q = 0; q < 9; ++q) {
+      p[2 * q] = s[q];
+      p[2 * q + 1] = cc[q];
     }
-    __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(kWG) void k_energy_final(Dev d, const double *part, int parts) {
+  __shared__ double sh[kWG / 64][18];
+  const int c = blockIdx.x;
+  double s[9], cc[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) s[q] = cc[q] = 0.0;
+  for (int y = threadIdx.x; y < parts; y += kWG) {
+    const double *p = part + 18 * ((int64_t)c * parts + y);
+    for (int q = 0; q < 9; ++q) {
+      cc[q] += p[2 * q + 1];
+      neu_add(s[q], cc[q], p[2 * q]);
+    }
+  }
+  energy_block(s, cc, sh);
   if (threadIdx.x == 0) {
-    double *o = d.eout + 9 * (int64_t)c;
-    o[0] = out[0];
-    o[1] = out[1];
-    o[2] = out[0] + out[1] + out[8];
-    for (int q = 0; q < 6; ++q) o[3 + q] = out[2 + q];
+    double t[9];
+    for (int q = 0; q < 9; ++q) t[q] = s[q] + cc[q];
+    energy_out(d, c, t);
   }
 }
 
@@ -2894,14 +2991,46 @@ __global__ void k_get_state(Dev d, double *x, double *v, double *a, double *jk,
   }
 }
 
-// set_state pass 1: copy in, validate levels, cluster time = max tick.
-__global__ void k_set_state1(Dev d, const double *x, const double *v,
-                             const double *a, const double *jk,
-                             const int64_t *tick, const int8_t *level,
-                             int lmin, int lmax) {
+// set_state pass 1: copy in, validate levels, cluster time = max tick.  Each
+// block takes `per` particles in a row (a multiple of kWG) and keeps its
+// cluster's level counts and latest tick in LDS until the cluster changes:
+// two atomics per particle on the same few words took 0.75 ms at 2^16
+// particles and 2.99 ms at 2^18 (5.7 ns each), against 8 and 23 us.
+__global__ __launch_bounds__(kWG) void k_set_state1(Dev d, const double *x, const double *v,
+                                                    const double *a, const double *jk,
+                                                    const int64_t *tick, const int8_t *level,
+                                                    int lmin, int lmax, int64_t per) {
+  __shared__ int lh[kLevels];
+  __shared__ unsigned long long tmax;
   const int64_t n = d.n;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t b0 = (int64_t)blockIdx.x * per;
+  const int64_t b1 = (b0 + per < n) ? b0 + per : n;
+  int cur = -1;                 // cluster the LDS counts belong to
+  if (threadIdx.x < kLevels) lh[threadIdx.x] = 0;
+  if (threadIdx.x == 0) tmax = 0;
+  __syncthreads();
+  auto flush = [&]() {          // by the whole block
+    __syncthreads();
+    if (threadIdx.x < kLevels) {
+      if (lh[threadIdx.x]) atomicAdd(&d.hist[cur * kLevels + threadIdx.x], lh[threadIdx.x]);
+      lh[threadIdx.x] = 0;
+    }
+    if (threadIdx.x == 0) {
+      if (tmax) atomicMax((unsigned long long *)&d.T[cur], tmax);
+      tmax = 0;
+    }
+    __syncthreads();
+  };
+  for (int64_t i0 = b0; i0 < b1; i0 += kWG) {
+    const int64_t last = (i0 + kWG < b1) ? i0 + kWG - 1 : b1 - 1;
+    const int c0 = d.cid[i0];
+    const bool same = c0 == d.cid[last];
+    if (same && c0 != cur) {
+      if (cur >= 0) flush();
+      cur = c0;
+    }
+    const int64_t i = i0 + threadIdx.x;
+    if (i >= b1) continue;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       d.x[c * n + i] = x[3 * i + c];
@@ -2917,10 +3046,16 @@ __global__ void k_set_state1(Dev d, const double *x, const double *v,
       atomicOr(d.err, kErrState);
       continue;
     }
-    const int c = d.cid[i];
-    atomicMax((unsigned long long *)&d.T[c], (unsigned long long)tk);
-    atomicAdd(&d.hist[c * kLevels + lv], 1);
+    if (same) {
+      if (tk) atomicMax(&tmax, (unsigned long long)tk);
+      atomicAdd(&lh[lv], 1);
+    } else {
+      const int c = d.cid[i];
+      atomicMax((unsigned long long *)&d.T[c], (unsigned long long)tk);
+      atomicAdd(&d.hist[c * kLevels + lv], 1);
+    }
   }
+  if (cur >= 0) flush();
 }
 
 // set_state pass 2: tick multiple of the step and tick <= T < tick + step.
@@ -3333,10 +3468,19 @@ hipError_t launch_api_finalize(const Dev &d, const RawSrc &r, hipStream_t s) {
 }
 
 hipError_t launch_energy_reduce(const Dev &d, hipStream_t s) {
+  // one workgroup per kWG particles of the mean cluster, at most 256; their
+  // sums (18 doubles each) lie in fsum, which holds 6 per particle
+  int64_t parts = d.n / ((int64_t)d.C * kWG);
+  if (parts > kWG) parts = kWG;
+  if (parts < 1) parts = 1;
+  const dim3 g((unsigned)d.C, (unsigned)parts);
   if (d.fld.on)
-    hipLaunchKernelGGL(k_energy_reduce<true>, dim3(d.C), dim3(kWG), 0, s, d);
+    hipLaunchKernelGGL(k_energy_reduce<true>, g, dim3(kWG), 0, s, d, d.fsum);
   else
-    hipLaunchKernelGGL(k_energy_reduce<false>, dim3(d.C), dim3(kWG), 0, s, d);
+    hipLaunchKernelGGL(k_energy_reduce<false>, g, dim3(kWG), 0, s, d, d.fsum);
+  if (parts > 1)
+    hipLaunchKernelGGL(k_energy_final, dim3((unsigned)d.C), dim3(kWG), 0, s, d,
+                       (const double *)d.fsum, (int)parts);
   return hipGetLastError();
 }
 
@@ -3363,8 +3507,10 @@ hipError_t launch_set_state(const Dev &d, const double *x, const double *v,
                             const int64_t *tick, const int8_t *level,
                             int level_min, int level_max, hipStream_t s) {
   // T and hist are cleared by the caller (fill kernels) beforehand
-  hipLaunchKernelGGL(k_set_state1, dim3(grid_for(d.n)), dim3(kWG), 0, s, d, x,
-                     v, a, jk, tick, level, level_min, level_max);
+  // at most 1024 blocks, each a run of whole kWG pieces
+  const int64_t per = ((d.n + 1023) / 1024 + kWG - 1) / kWG * kWG;
+  hipLaunchKernelGGL(k_set_state1, dim3((unsigned)((d.n + per - 1) / per)), dim3(kWG), 0, s, d,
+                     x, v, a, jk, tick, level, level_min, level_max, per);
   int64_t need = d.n > d.C ? d.n : d.C;
   hipLaunchKernelGGL(k_set_state2, dim3(grid_for(need)), dim3(kWG), 0, s, d);
   return hipGetLastError();
