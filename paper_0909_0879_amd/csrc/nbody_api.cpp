@@ -382,12 +382,48 @@ int harvest_events(nbody_ctx *c);
 // records in the compaction too (one launch fewer per step).
 bool rec_in_compact(const nbody_ctx *c) { return nbk::plan_fused(c->d); }
 
+// Which force kernels an evaluation enqueues.  kRouteDevice: both, the record
+// flag decides (block steps, several clusters); otherwise the host knows the
+// active count and the plan's i-slots and enqueues one: kRouteRaw the
+// workgroup kernel filling its tiles itself, kRouteLds the same over records,
+// kRouteSb the broadcast kernel.  An empty launch costs about 4 us.
+enum Route { kRouteDevice, kRouteRaw, kRouteLds, kRouteSb };
+
+int bucket_of(int64_t na) {
+  int b = 0;
+  while (b + 1 < nbk::kBuckets && (na >> (b + 1)) > 0) ++b;
+  return b;
+}
+
+// Route of an evaluation with every particle of the state active.
+Route state_route(const nbody_ctx *c, bool acc_only) {
+  if (c->C != 1) return kRouteDevice;
+  const bool wide = c->tune.i_slots[bucket_of(c->n)] == nbk::kWG;
+  return wide && (acc_only ? c->sba : c->sb) ? kRouteSb : kRouteLds;
+}
+
+// Route of na entries against n_j caller's particles.  Records pay when each
+// is read by many i: from one entry in 16 on, and, where the broadcast kernel
+// takes them, from one wide item's worth of entries on in the mixed forms and
+// the acceleration-only ones (1001 of 262144 mixed, two passes: 570 -> 430 us;
+// the tile fill converts each j again for every 64 or 256 entries).
+Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
+  if (c->C != 1) return kRouteDevice;
+  if (n_j > c->d.n) return kRouteRaw;       // the buffer holds d.n records
+  const bool wide = c->tune.i_slots[bucket_of(na)] == nbk::kWG && (acc_only ? c->sba : c->sb);
+  const bool many = wide && na >= nbk::kWG && (acc_only || is_mixed(c->prec));
+  if (!many && na * 16 < n_j) return kRouteRaw;
+  return wide ? kRouteSb : kRouteLds;
+}
+
 // Launch the force kernel, bracketed by timing events when profiling.
 // rec_kind >= 0 (a PlanKind): build the evaluation's j records first when its
-// active set is large, and let the broadcast kernel take it when enabled.
+// active set is large (build: unless an earlier launch did), and let the
+// broadcast kernel take it when enabled.
 int force_launch(nbody_ctx *c, int mode, int src, int K, const nbk::RawSrc *raw,
                  const int32_t *list, int grid, hipStream_t s, int rec_kind = -1,
-                 nbk::NearSpec nr = nbk::NearSpec{nbk::kNearNone, 0.0f}) {
+                 nbk::NearSpec nr = nbk::NearSpec{nbk::kNearNone, 0.0f},
+                 Route route = kRouteDevice, bool build = true) {
   const bool prof = c->profiling && s == c->stream;
   const bool use_pred = rec_kind >= 0;
   const bool mixed_step = rec_kind == nbk::kPlanStep && nbk::mode_mixed(mode) &&
@@ -400,21 +436,25 @@ int force_launch(nbody_ctx *c, int mode, int src, int K, const nbk::RawSrc *raw,
   const bool rec_only = mixed_step || rec_kind == nbk::kPlanState;
   const bool sb = nbk::mode_acc_only(mode) ? c->sba : c->sb;
   const bool sb_only = mixed_step && c->step_sb_only;
-  if (use_pred && !(rec_kind == nbk::kPlanStep && rec_in_compact(c)))
-    NB_HIP(nbk::launch_records(c->d, mode, rec_kind, raw, sb, rec_only, sb_only, s));
+  if (use_pred && build && route != kRouteRaw &&
+      !(rec_kind == nbk::kPlanStep && rec_in_compact(c)))
+    NB_HIP(nbk::launch_records(c->d, mode, rec_kind, raw,
+                               route == kRouteDevice ? sb : route == kRouteSb,
+                               rec_only || route != kRouteDevice, sb_only, s));
   if (prof && c->ev_used == kEvPairs) {
     int rc = harvest_events(c);
     if (rc) return rc;
   }
   if (prof) NB_HIP(hipEventRecord(c->ev[2 * c->ev_used], s));
-  if (!sb_only)
+  if (!sb_only && route != kRouteSb)
     NB_HIP(nbk::launch_force(c->d, mode, rec_only ? nbk::kSrcRec : src, K, raw, list,
-                              use_pred ? nbk::kRoleMain : nbk::kRoleAlways, nr,
+                              use_pred && route != kRouteRaw ? nbk::kRoleMain : nbk::kRoleAlways,
+                              nr,
                               rec_only ? (nbk::mode_acc_only(mode) ? c->grid_acc_rec
                                                                    : c->grid_rec)
                                        : grid,
                               s));
-  if (use_pred && sb)
+  if (use_pred && sb && (route == kRouteDevice || route == kRouteSb))
     NB_HIP(nbk::launch_force_sb(c->d, mode, K, raw, list, nr,
                                 nbk::mode_acc_only(mode) ? c->grid_acc_sb : c->grid_sb, s));
   if (small)
@@ -480,13 +520,21 @@ int sum_and_refine(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk
                    hipStream_t s, bool acc_only, nbk::NearSpec nr,
                    const nbk::CorrectSpec *corr = nullptr) {
   const float ratio = refine_ratio(c);
+  // nbody_forces / nbody_accel without a re-evaluation: sums to the caller
+  if (raw && ratio <= 0.0f && c->C == 1) {
+    NB_HIP(nbk::launch_sum_out(c->d, *raw, s));
+    return NBODY_OK;
+  }
   const nbk::Tuning t1 = device_tuning(c, 1);
   const bool api = raw != nullptr;
   const int ref_kind = api ? nbk::kPlanApiRefine : nbk::kPlanRefine;
   const int64_t api_nj = api ? raw->n_j : 0;
   NB_HIP(nbk::launch_sum_and_flag(c->d, list, na_host, ratio, nr, false, t1, ref_kind, api_nj,
                                   corr != nullptr, s));
-  if (ratio <= 0.0f) return NBODY_OK;
+  if (ratio <= 0.0f) {
+    if (raw) NB_HIP(nbk::launch_api_finalize(c->d, *raw, s));
+    return NBODY_OK;
+  }
   if (!nbk::plan_fused(c->d))
     NB_HIP(nbk::launch_plan(c->d, t1, ref_kind, api_nj, false, s));
   const int grid = acc_only ? (api ? c->grid_ref_acc_raw : c->grid_ref_acc_state)
@@ -494,28 +542,28 @@ int sum_and_refine(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk
   int rc = force_launch(c, acc_only ? nbk::kModeFP64Acc : nbk::kModeFP64,
                         api ? nbk::kSrcRaw : nbk::kSrcState, 1, raw, c->d.ref_i, grid, s);
   if (rc) return rc;
-  NB_HIP(nbk::launch_refine_finalize(c->d, corr, s));
+  NB_HIP(nbk::launch_refine_finalize(c->d, corr, raw, s));
   return NBODY_OK;
 }
 
 // One mixed evaluation with jerk when no jerk estimate is at hand (initial
 // state, full re-evaluations, nbody_forces): a first pass without near pairs
 // gives each entry's jerk, from which the second pass takes its near-pair
-// thresholds.  `launch` enqueues the force launch(es) of one pass (the plan
-// and the records stay valid; the item counters are reset in between).
+// thresholds.  `launch` enqueues the force launch(es) of one pass, told whether
+// it is the first (the plan and the records stay valid; the sums in between
+// reset the item counters).
 template <class F>
 int two_pass(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk::RawSrc *raw,
              hipStream_t s, int mode, F launch) {
   const nbk::NearSpec first = near_spec(c, mode, nbk::kNearNone);
   const nbk::NearSpec second = near_spec(c, mode, nbk::kNearList);
-  int rc = launch(first);
+  int rc = launch(first, true);
   if (rc) return rc;
   if (second.src == nbk::kNearList) {
     const nbk::Tuning t1 = device_tuning(c, 1);
     NB_HIP(nbk::launch_sum_and_flag(c->d, list, na_host, 0.0f, second, true, t1, 0, 0, false,
                                     s));
-    NB_HIP(nbk::launch_fill32(c->d.work, 0, 2, s));
-    if ((rc = launch(second))) return rc;
+    if ((rc = launch(second, false))) return rc;
   }
   return sum_and_refine(c, list, na_host, raw, s, nbk::mode_acc_only(mode), second);
 }
@@ -593,10 +641,10 @@ int full_evaluation_into_state(nbody_ctx *c) {
   // all particles start at T = T_next = 0, so the re-evaluation plan
   // (predicting to T_next) sees the same positions
   int rc = two_pass(c, c->d.active, -1, nullptr, c->stream, mode_of(c),
-                    [&](nbk::NearSpec nr) {
+                    [&](nbk::NearSpec nr, bool first) {
                       return force_launch(c, mode_of(c), nbk::kSrcState, c->K, nullptr,
                                           c->d.active, c->grid_state, c->stream,
-                                          nbk::kPlanState, nr);
+                                          nbk::kPlanState, nr, state_route(c, false), first);
                     });
   if (rc) return rc;
   NB_HIP(nbk::launch_init_levels(c->d, c->eta_start, c->dt_shared, c->lmin, c->lmax,
@@ -620,10 +668,11 @@ int check_t_end(const nbody_ctx *c, double t_end, int64_t *tend_out) {
 }
 
 // nbody_forces / nbody_accel: the caller's j arrays, chunks of at most
-// cap_active i entries.
+// cap_active i entries.  eps2 (host): the softening of a caller without a
+// context, written with the plan.
 int api_forces(nbody_ctx *c, bool acc_only, const int32_t *i_active, int64_t n_active,
                const double *xj, const double *vj, const double *mj, int64_t n_j, double *acc,
-               double *jerk) {
+               double *jerk, const double *eps2 = nullptr) {
   if (!c) return fail(NBODY_EINVAL, "context is NULL");
   if (n_active < 0) return fail(NBODY_EINVAL, "n_active < 0");
   if (n_active == 0) return NBODY_OK;
@@ -646,15 +695,21 @@ int api_forces(nbody_ctx *c, bool acc_only, const int32_t *i_active, int64_t n_a
     r.n_active = (n_active - k0 < cap) ? n_active - k0 : cap;
     r.acc = acc + 3 * k0;
     r.jerk = jerk ? jerk + 3 * k0 : nullptr;
-    NB_HIP(nbk::launch_api_group(c->d, r, t, c->stream));
-    if (c->prec == NBODY_MIXED && !acc_only) NB_HIP(nbk::launch_vref(c->d, &r, c->stream));
-    if (c->C > 1) NB_HIP(nbk::launch_plan(c->d, t, nbk::kPlanApi, r.n_j, false, c->stream));
-    int rc = two_pass(c, r.i_active, r.n_active, &r, c->stream, mode, [&](nbk::NearSpec nr) {
-      return force_launch(c, mode, nbk::kSrcRaw, K, &r, r.i_active, grid, c->stream,
-                          nbk::kPlanApi, nr);
-    });
+    const bool vref = c->prec == NBODY_MIXED && !acc_only;
+    if (c->C == 1) {
+      NB_HIP(nbk::launch_api_single(c->d, r, t, vref, eps2, c->stream));
+    } else {
+      NB_HIP(nbk::launch_api_group(c->d, r, c->stream));
+      if (vref) NB_HIP(nbk::launch_vref(c->d, &r, c->stream));
+      NB_HIP(nbk::launch_plan(c->d, t, nbk::kPlanApi, r.n_j, false, c->stream));
+    }
+    const Route route = api_route(c, acc_only, r.n_active, n_j);
+    int rc = two_pass(c, r.i_active, r.n_active, &r, c->stream, mode,
+                      [&](nbk::NearSpec nr, bool first) {
+                        return force_launch(c, mode, nbk::kSrcRaw, K, &r, r.i_active, grid,
+                                            c->stream, nbk::kPlanApi, nr, route, first);
+                      });
     if (rc) return rc;
-    NB_HIP(nbk::launch_api_finalize(c->d, r, c->stream));
   }
   return NBODY_OK;
 }
@@ -780,22 +835,36 @@ int nbody_step_symplectic(nbody_ctx *c, int scheme, double h, int64_t n_steps,
   // with one cluster the kernel before each evaluation (the all-active
   // setup, then every kick-drift) writes its plan
   NB_HIP(nbk::launch_all_active(c->d, t, c->stream));
-  auto evaluate = [&](hipStream_t s) -> int {
-    if (c->C > 1) NB_HIP(nbk::launch_plan(c->d, t, nbk::kPlanState, 0, false, s));
-    int r = force_launch(c, mode, nbk::kSrcState, c->Ka, nullptr, c->d.active, c->grid_acc_state,
-                         s, nbk::kPlanState);
-    if (r) return r;
+  const Route route = state_route(c, true);
+  const int rec_on = route == kRouteSb ? 2 : 1;
+  // one cluster: the sweep before an evaluation also builds its records, and
+  // in FP64 (no re-evaluation) takes the sums of the evaluation before
+  const bool fused = c->C == 1;
+  const bool sum_in_sweep = fused && refine_ratio(c) <= 0.0f && c->prec == NBODY_FP64;
+  const int rec_mode = fused ? mode_of(c) : -1;
+  auto sums = [&](hipStream_t s) -> int {
     return sum_and_refine(c, c->d.active, -1, nullptr, s, /*acc_only=*/true,
                           nbk::NearSpec{nbk::kNearNone, 0.0f});
+  };
+  auto evaluate = [&](hipStream_t s, bool build) -> int {
+    if (c->C > 1) NB_HIP(nbk::launch_plan(c->d, t, nbk::kPlanState, 0, false, s));
+    int r = force_launch(c, mode, nbk::kSrcState, c->Ka, nullptr, c->d.active, c->grid_acc_state,
+                         s, nbk::kPlanState, nbk::NearSpec{nbk::kNearNone, 0.0f}, route, build);
+    if (r || sum_in_sweep) return r;
+    return sums(s);
   };
   // one step: every stage kicks (merging the previous stage's half kick),
   // drifts and evaluates; returns the half kick still owed
   auto enqueue_step = [&](hipStream_t s, double pending, bool check, double *owed) -> int {
     for (double wk : w) {
       const double cw = wk * h;
-      NB_HIP(nbk::launch_sym_kick_drift(c->d, pending + 0.5 * cw, cw, check, t, s));
+      if (sum_in_sweep)
+        NB_HIP(nbk::launch_sum_kick_drift(c->d, pending + 0.5 * cw, cw, check, rec_on, s));
+      else
+        NB_HIP(nbk::launch_sym_kick_drift(c->d, pending + 0.5 * cw, cw, check, t, rec_mode,
+                                          rec_on, s));
       check = false;
-      int r = evaluate(s);
+      int r = evaluate(s, !fused);
       if (r) return r;
       pending = 0.5 * cw;
     }
@@ -804,7 +873,7 @@ int nbody_step_symplectic(nbody_ctx *c, int scheme, double h, int64_t n_steps,
   };
   // the state's acceleration was taken at predicted positions: evaluate
   // at the current ones first
-  if ((rc = evaluate(c->stream))) return rc;
+  if ((rc = evaluate(c->stream, true))) return rc;
   double pending = 0.0;
   if ((rc = enqueue_step(c->stream, 0.0, true, &pending))) return rc;
   const int64_t evals = 1 + n_steps * (int64_t)w.size();
@@ -842,6 +911,7 @@ int nbody_step_symplectic(nbody_ctx *c, int scheme, double h, int64_t n_steps,
       if ((st & 63) == 63 && (rc = readback(c))) return rc;
     }
   }
+  if (sum_in_sweep && (rc = sums(c->stream))) return rc;
   NB_HIP(nbk::launch_sym_kick(c->d, pending, c->stream));
   NB_HIP(nbk::launch_sym_advance(c->d, span, c->stream));
   for (int k = 0; k < c->C; ++k) c->T_host[k] += span;
@@ -1200,14 +1270,8 @@ int nbody_forces_noalloc(int precision, double eps, const int32_t *i_active, int
     if (rc) return rc;
     g.grids_prec = precision;
   }
-  // the cluster table of this call: [0, n_j) and eps^2 (kernels, no copies)
   const double eps2 = eps * eps;
-  int64_t eps2_bits;
-  std::memcpy(&eps2_bits, &eps2, sizeof eps2_bits);
-  NB_HIP(nbk::launch_set_word64(c->d.coff, 0, c->stream));
-  NB_HIP(nbk::launch_set_word64(c->d.coff + 1, n_j, c->stream));
-  NB_HIP(nbk::launch_set_word64((int64_t *)c->d.eps2, eps2_bits, c->stream));
-  return api_forces(c, false, i_active, n_active, xj, vj, mj, n_j, acc, jerk);
+  return api_forces(c, false, i_active, n_active, xj, vj, mj, n_j, acc, jerk, &eps2);
 }
 
 }  // extern "C"

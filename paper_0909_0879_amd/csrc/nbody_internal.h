@@ -216,6 +216,10 @@ struct RawSrc {                 // caller arrays for nbody_forces
   double *acc, *jerk;          // (n_active, 3) outputs
 };
 
+struct ApiOut {                 // the caller's output arrays (jerk may be null)
+  double *acc, *jerk;
+};
+
 hipError_t launch_init_state(const Dev &d, const double *m, const double *x,
                              const double *v, hipStream_t s);
 // Every particle active; with one cluster also the kPlanState plan (tuning t).
@@ -261,7 +265,9 @@ hipError_t launch_sum_and_flag(const Dev &d, const int32_t *list, int64_t na_hos
 // Overwrite fsum of the re-evaluated entries with their FP64 sums; corr
 // (block steps): and apply the corrector to every active particle, so no
 // launch_correct follows.
-hipError_t launch_refine_finalize(const Dev &d, const CorrectSpec *corr, hipStream_t s);
+// out (nbody_forces, nbody_accel): write all entries to its arrays instead.
+hipError_t launch_refine_finalize(const Dev &d, const CorrectSpec *corr, const RawSrc *out,
+                                  hipStream_t s);
 // Which work a force launch takes.  The plan splits the items in two:
 // [0, work[2]) for the main launches, [work[2], total) for the small-step
 // launch.  kRoleAlways: the main items, whatever the record flag
@@ -291,8 +297,13 @@ int force_sb_grid_size(int mode, int K, int device);
 // Symplectic drivers: kick (v += ck a, a from fsum) then drift (x += cd v)
 // (with one cluster also the next evaluation's kPlanState plan, tuning t);
 // final kick; advance all times by dticks.
+// rec_mode >= 0 (mixed, one cluster): the kick-drift also writes the j records
+// and the record flag rec_on, so no launch_records follows.  FP64, one cluster:
+// launch_sum_kick_drift takes the row sums as well (the plan stays).
 hipError_t launch_sym_kick_drift(const Dev &d, double ck, double cd, bool check,
-                                 const Tuning &t, hipStream_t s);
+                                 const Tuning &t, int rec_mode, int rec_on, hipStream_t s);
+hipError_t launch_sum_kick_drift(const Dev &d, double ck, double cd, bool check, int rec_on,
+                                 hipStream_t s);
 hipError_t launch_sym_kick(const Dev &d, double ck, hipStream_t s);
 hipError_t launch_sym_advance(const Dev &d, int64_t dticks, hipStream_t s);
 // Each cluster's reference velocity for the FP64-difference mixed records
@@ -307,9 +318,15 @@ hipError_t launch_correct(const Dev &d, double eta, double dt_shared,
 hipError_t launch_init_levels(const Dev &d, double eta_start,
                               double dt_shared, int level_min, int level_max,
                               hipStream_t s);
-// nbody_forces / nbody_accel: per-cluster offsets of the caller's active list
-// (and its index checks); with one cluster also the kPlanApi plan (tuning t).
-hipError_t launch_api_group(const Dev &d, const RawSrc &r, const Tuning &t, hipStream_t s);
+// nbody_forces / nbody_accel with several clusters: per-cluster offsets of the
+// caller's active list (and its index checks).
+hipError_t launch_api_group(const Dev &d, const RawSrc &r, hipStream_t s);
+// The same with one cluster: the kPlanApi plan (tuning t), zeroed flag counts,
+// the reference velocity (vref) and the cluster's eps^2 (eps2, may be null).
+hipError_t launch_api_single(const Dev &d, const RawSrc &r, const Tuning &t, bool vref,
+                             const double *eps2, hipStream_t s);
+// Row sums of a one-cluster evaluation into the caller's arrays.
+hipError_t launch_sum_out(const Dev &d, const RawSrc &r, hipStream_t s);
 hipError_t launch_api_finalize(const Dev &d, const RawSrc &r, hipStream_t s);
 hipError_t launch_energy_reduce(const Dev &d, hipStream_t s);
 hipError_t launch_set_word64(int64_t *p, int64_t v, hipStream_t s);

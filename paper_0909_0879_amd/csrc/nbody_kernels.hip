@@ -1208,9 +1208,8 @@ __device__ int initial_level(const double *a, const double *j, double eta_s,
 // evaluation share it; one near the bulk velocity keeps |v - v_ref| of
 // order the dispersion.  raw.x set: from a caller's arrays (one cluster:
 // its n_j particles).
-__global__ __launch_bounds__(kWG) void k_vref(Dev d, RawSrc raw) {
+__device__ __forceinline__ void vref_block(const Dev &d, const RawSrc &raw, int c) {
   __shared__ double sh[4][kWG];
-  const int c = blockIdx.x;
   const bool api = raw.x != nullptr;
   const int64_t b = (api && d.C == 1) ? 0 : d.coff[c];
   const int64_t nc = (api && d.C == 1 && raw.n_j > 0) ? raw.n_j : d.coff[c + 1] - b;
@@ -1234,6 +1233,10 @@ __global__ __launch_bounds__(kWG) void k_vref(Dev d, RawSrc raw) {
     __syncthreads();
   }
   if (k < 3) d.vref[3 * c + k] = sh[3][0] > 0.0 ? sh[k][0] / sh[3][0] : 0.0;
+}
+
+__global__ __launch_bounds__(kWG) void k_vref(Dev d, RawSrc raw) {
+  vref_block(d, raw, blockIdx.x);
 }
 
 __global__ void k_init_state(Dev d, const double *m, const double *x,
@@ -2149,38 +2152,75 @@ __global__ __launch_bounds__(kWG) void k_init_levels(Dev d, double eta_s,
     atomicAdd(&d.hist[d.cid[i0] * kLevels + threadIdx.x], lh[threadIdx.x]);
 }
 
+// nbody_forces / nbody_accel of one cluster: everything its evaluation needs
+// besides the records, in one workgroup: the plan (the active count is the
+// caller's), the zeroed flag counts, the reference velocity (want_vref), and
+// eps^2 of a caller without a context (set_eps).  One launch where the plan,
+// the reference velocity, the counts and the three words of the no-allocation
+// entry took six, each about 4 us of a call of 35.
+__global__ __launch_bounds__(kWG) void k_api_single(Dev d, RawSrc raw, Tuning tu, int want_vref,
+                                                    int set_eps, double eps2) {
+  if (threadIdx.x == kWG - 1) {
+    if (set_eps) d.eps2[0] = eps2;
+    d.act_off[0] = 0;
+    d.act_off[1] = (int32_t)raw.n_active;
+    *d.pred_on = 0;
+    plan_single(d, tu, kPlanApi, raw.n_j, 0, (int32_t)raw.n_active);
+  }
+  for (int b = threadIdx.x; b < d.nblk; b += kWG) d.flag_cnt[b] = 0;
+  if (want_vref) vref_block(d, raw, 0);
+}
+
 // nbody_forces with several clusters: offsets of each cluster's group in
 // i_active (which must be grouped by non-decreasing cluster id).
-__global__ void k_api_group(Dev d, const int32_t *ia, int64_t na, Tuning tu, int64_t api_nj) {
+__global__ void k_api_group(Dev d, const int32_t *ia, int64_t na) {
   const int64_t gt = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int C = d.C;
-  // one cluster: the active count is the caller's, so plan here
-  if (C == 1 && gt == 0) plan_single(d, tu, kPlanApi, api_nj, 0, (int32_t)na);
   auto key = [&](int64_t k) -> int {
     const int32_t i = ia[k];
     if (i < 0 || i >= d.n) return C;     // invalid: sorts last
     return d.cid[i];
   };
-  // with one cluster the j set is the caller's (any n_j): the force kernel
-  // checks i against it; with several, i must index the context's clusters
-  if (C > 1) {
-    for (int64_t k = gt; k < na; k += (int64_t)gridDim.x * blockDim.x) {
-      const int32_t i = ia[k];
-      if (i < 0 || i >= d.n) atomicOr(d.err, (int)kErrIndex);
-      if (k > 0 && key(k) < key(k - 1)) atomicOr(d.err, (int)kErrIndex);
-    }
+  for (int64_t k = gt; k < na; k += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t i = ia[k];
+    if (i < 0 || i >= d.n) atomicOr(d.err, (int)kErrIndex);
+    if (k > 0 && key(k) < key(k - 1)) atomicOr(d.err, (int)kErrIndex);
   }
   if (gt <= C) {
-    if (C == 1) {
-      d.act_off[gt] = (gt == 0) ? 0 : (int32_t)na;
-    } else {
-      int64_t lo = 0, hi = na;   // first k with key(k) >= gt
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (key(mid) < gt) lo = mid + 1; else hi = mid;
-      }
-      d.act_off[gt] = (int32_t)lo;
+    int64_t lo = 0, hi = na;   // first k with key(k) >= gt
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (key(mid) < gt) lo = mid + 1; else hi = mid;
     }
+    d.act_off[gt] = (int32_t)lo;
+  }
+}
+
+// One entry's forces into the caller's arrays.
+__device__ __forceinline__ void api_store(const Dev &d, const ApiOut &o, int64_t k,
+                                          const double (&f)[6]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    o.acc[3 * k + q] = f[q];
+    if (o.jerk) o.jerk[3 * k + q] = f[3 + q];
+  }
+  if (!(finite3(f) && finite3(f + 3))) atomicOr(d.err, (int)kErrNonFinite);
+}
+
+// Row sums straight into the caller's arrays (evaluations of one cluster
+// without a re-evaluation), as k_sum_flag forms them.
+__global__ __launch_bounds__(kWG) void k_sum_out(Dev d, ApiOut o) {
+  const int lane = threadIdx.x & 63;
+  const int nw = d.sum_prefix[1];
+  const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const ClusterPlan cp = d.plan_c[0];
+  for (int w = wave0; w < nw; w += nwaves) {
+    const int slot = (w << (6 - cp.glog)) + (lane >> cp.glog);
+    const bool valid = slot < cp.na;
+    double f[6], tmax, tf1;
+    group_sum_rows(d, cp, slot, cp.glog, valid, f, tmax, tf1);
+    if (valid && (lane & ((1 << cp.glog) - 1)) == 0) api_store(d, o, slot, f);
   }
 }
 
@@ -2585,31 +2625,100 @@ __device__ __forceinline__ void sym_acc(const Dev &d, int64_t i, double acc[3]) 
   }
 }
 
-// Kick by ck, then drift by cd.  check: every particle must sit at its
-// cluster's time (no particle in the middle of a block step).
+// Kick particle i by ck with the pair sums acc (plus the field), drift it by
+// cd; returns whether the state stays finite.
 template <bool FIELD>
-__global__ void k_sym_kick_drift(Dev d, double ck, double cd, int check, Tuning tu,
-                                 int plan_kind) {
+__device__ __forceinline__ bool kick_drift_one(const Dev &d, int64_t i, double ck, double cd,
+                                               const double acc[3], double xn[3], double vn[3]) {
   const int64_t n = d.n;
+  bool fin = true;
+  double f[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) xn[c] = d.x[c * n + i];
+  if (FIELD) {
+    double fj[3];
+    const double zero[3] = {0.0, 0.0, 0.0};
+    ext_field(d.fld, xn, zero, f, fj);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    double v = d.v[c * n + i];
+    if (ck != 0.0) v = fma(ck, FIELD ? acc[c] + f[c] : acc[c], v);
+    vn[c] = v;
+    xn[c] = fma(cd, v, xn[c]);
+    d.v[c * n + i] = v;
+    d.x[c * n + i] = xn[c];
+    fin = fin && isfinite(xn[c]) && isfinite(v);
+  }
+  return fin;
+}
+
+// FP64, one cluster: the row sums of the evaluation before, the kick, the
+// drift and the j record of the evaluation that follows, in one launch (the
+// plan stays: every particle is active in each of them; rec_on: the record
+// flag).  Four launches of about 4 us each before; sixth order at N = 4096:
+// 4.1 -> 3.0 ms for 112 evaluations.
+template <bool FIELD>
+__global__ __launch_bounds__(kWG) void k_sum_kick_drift(Dev d, double ck, double cd, int check,
+                                                        int rec_on) {
+  const int lane = threadIdx.x & 63;
+  const int nw = d.sum_prefix[1];
+  const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const ClusterPlan cp = d.plan_c[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    d.work[0] = 0;
+    d.work[1] = 0;
+    *d.pred_on = rec_on;
+  }
+  JRec64 *pred = reinterpret_cast<JRec64 *>(d.pred);
+  for (int w = wave0; w < nw; w += nwaves) {
+    const int slot = (w << (6 - cp.glog)) + (lane >> cp.glog);
+    const bool valid = slot < cp.na;
+    double f[6], tmax, tf1;
+    group_sum_rows(d, cp, slot, cp.glog, valid, f, tmax, tf1);
+    if (!valid || (lane & ((1 << cp.glog) - 1)) != 0) continue;
+    const int64_t i = slot;               // every particle is active, in order
+    if (check && d.tick[i] != d.T[0]) atomicOr(d.err, kErrState);
+    double x[3], v[3];
+    if (!kick_drift_one<FIELD>(d, i, ck, cd, f, x, v)) atomicOr(d.err, (int)kErrNonFinite);
+    JRec64 r;
+    make_rec(x, v, d.m[i], (int32_t)i, r, 1.0, nullptr);
+    pred[i] = r;
+  }
+}
+
+// Kick by ck, then drift by cd.  check: every particle must sit at its
+// cluster's time (no particle in the middle of a block step).  RMODE >= 0
+// (one cluster): also writes the particles' j records for the evaluation that
+// follows, the record flag rec_on and the zeroed flag counts, in place of the
+// record kernel.
+template <bool FIELD, int RMODE>
+__global__ void k_sym_kick_drift(Dev d, double ck, double cd, int check, Tuning tu,
+                                 int plan_kind, int rec_on) {
+  const int64_t n = d.n;
+  if constexpr (RMODE >= 0) {
+    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < d.nblk; b += gridDim.x * blockDim.x)
+      d.flag_cnt[b] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *d.pred_on = rec_on;
+  }
   // one cluster: plan the evaluation that follows (every particle active)
   if (blockIdx.x == 0 && threadIdx.x == 0 && plan_kind >= 0)
     plan_single(d, tu, plan_kind, 0, 0, (int32_t)n);
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     if (check && d.tick[i] != d.T[d.cid[i]]) atomicOr(d.err, kErrState);
-    bool fin = true;
-    double acc[3];
-    sym_acc<FIELD>(d, i, acc);
+    double acc[3], x[3], v[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double v = d.v[c * n + i];
-      if (ck != 0.0) v = fma(ck, acc[c], v);
-      const double x = fma(cd, v, d.x[c * n + i]);
-      d.v[c * n + i] = v;
-      d.x[c * n + i] = x;
-      fin = fin && isfinite(x) && isfinite(v);
+    for (int c = 0; c < 3; ++c) acc[c] = d.fsum[6 * i + c];
+    if (!kick_drift_one<FIELD>(d, i, ck, cd, acc, x, v)) atomicOr(d.err, (int)kErrNonFinite);
+    if constexpr (RMODE >= 0) {
+      using Rec = typename Traits<RMODE>::Rec;
+      const double zero[3] = {0.0, 0.0, 0.0};     // velocities are not read
+      Rec r;
+      make_rec(x, v, d.m[i], (int32_t)i, r, mode_mixed(RMODE) ? mass_ref(d.m[0]) : 1.0, zero);
+      reinterpret_cast<Rec *>(d.pred)[i] = r;
     }
-    if (!fin) atomicOr(d.err, (int)kErrNonFinite);
   }
 }
 
@@ -2670,6 +2779,8 @@ __global__ __launch_bounds__(kWG) void k_sum_flag(Dev d, const int32_t *list, fl
                                                   float near_c, int near_src, int theta_out,
                                                   Tuning tu, int plan_kind) {
   const int lane = threadIdx.x & 63;
+  // the second pass of the same plan counts its items from zero
+  if (theta_out && blockIdx.x == 0 && threadIdx.x < 2) d.work[threadIdx.x] = 0;
   const int nw = d.sum_prefix[d.C];
   const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
@@ -2813,9 +2924,25 @@ __global__ __launch_bounds__(kWG) void k_rscatter(Dev d, const int32_t *list,
 // steps): that wave also corrects its particle, and blocks [ref_blocks,
 // gridDim.x) correct every other active entry from fsum, one thread each —
 // the whole corrector in this launch, after the FP64 pass (which predicts
-// from the state) has finished.
-template <bool CORR, bool FIELD>
-__global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, CorrectSpec cs) {
+// from the state) has finished.  OUT (nbody_forces, nbody_accel): the same
+// split writes the na entries to the caller's arrays.
+template <bool CORR, bool FIELD, bool OUT>
+__global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, CorrectSpec cs,
+                                                   ApiOut out, int64_t na_out) {
+  if constexpr (OUT) {
+    if ((int)blockIdx.x >= ref_blocks) {
+      const int64_t stride = (int64_t)((int)gridDim.x - ref_blocks) * kWG;
+      for (int64_t k = (int64_t)((int)blockIdx.x - ref_blocks) * kWG + threadIdx.x; k < na_out;
+           k += stride) {
+        if (d.rflag[k]) continue;           // written by its wave below
+        double f[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) f[q] = d.fsum[6 * k + q];
+        api_store(d, out, k, f);
+      }
+      return;
+    }
+  }
   __shared__ int lh[kLevels];
   LevelCounts lc{lh, -1};
   if constexpr (CORR) {
@@ -2855,8 +2982,12 @@ __global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, Correc
     group_sum_rows(d, cp, r - cp.act_off, 6, true, f, tmax, tf1);
     if ((threadIdx.x & 63) == 0) {
       const int64_t k = d.ref_k[r];
+      if constexpr (OUT) {
+        api_store(d, out, k, f);
+      } else {
 #pragma unroll
-      for (int q = 0; q < 6; ++q) d.fsum[6 * k + q] = f[q];
+        for (int q = 0; q < 6; ++q) d.fsum[6 * k + q] = f[q];
+      }
       if constexpr (CORR)
         // (a few entries a step: straight to the histogram, lc holds no cluster)
         correct_one<FIELD>(d, d.ref_i[r], c, f, cs.eta, cs.dt_shared, cs.lmin, cs.lmax, lc);
@@ -3276,14 +3407,34 @@ int force_grid_size(int mode, int src, int K, int device) {
 }
 
 hipError_t launch_sym_kick_drift(const Dev &d, double ck, double cd, bool check,
-                                 const Tuning &t, hipStream_t s) {
+                                 const Tuning &t, int rec_mode, int rec_on, hipStream_t s) {
   const int pk = d.C == 1 ? (int)kPlanState : -1;
+  const dim3 g(grid_for(d.n)), b(kWG);
+  if (rec_mode >= 0 && d.C != 1) return hipErrorInvalidValue;
+#define NB_CASE(F, M)                                                                     \
+  if ((bool)d.fld.on == F && rec_mode == M) {                                             \
+    hipLaunchKernelGGL((k_sym_kick_drift<F, M>), g, b, 0, s, d, ck, cd, check ? 1 : 0, t, \
+                       pk, rec_on);                                                       \
+    return hipGetLastError();                                                             \
+  }
+  NB_CASE(false, -1)
+  NB_CASE(true, -1)
+  NB_CASE(false, kModeMixed)
+  NB_CASE(true, kModeMixed)
+  NB_CASE(false, kModeMixed64)
+  NB_CASE(true, kModeMixed64)
+#undef NB_CASE
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_sum_kick_drift(const Dev &d, double ck, double cd, bool check, int rec_on,
+                                 hipStream_t s) {
+  if (d.C != 1) return hipErrorInvalidValue;
+  const dim3 g(grid_for(d.n * 64, kWG, 4096)), b(kWG);
   if (d.fld.on)
-    hipLaunchKernelGGL(k_sym_kick_drift<true>, dim3(grid_for(d.n)), dim3(kWG), 0, s, d, ck,
-                       cd, check ? 1 : 0, t, pk);
+    hipLaunchKernelGGL(k_sum_kick_drift<true>, g, b, 0, s, d, ck, cd, check ? 1 : 0, rec_on);
   else
-    hipLaunchKernelGGL(k_sym_kick_drift<false>, dim3(grid_for(d.n)), dim3(kWG), 0, s, d, ck,
-                       cd, check ? 1 : 0, t, pk);
+    hipLaunchKernelGGL(k_sum_kick_drift<false>, g, b, 0, s, d, ck, cd, check ? 1 : 0, rec_on);
   return hipGetLastError();
 }
 
@@ -3406,18 +3557,26 @@ hipError_t launch_sum_and_flag(const Dev &d, const int32_t *list, int64_t na_hos
   return hipGetLastError();
 }
 
-hipError_t launch_refine_finalize(const Dev &d, const CorrectSpec *corr, hipStream_t s) {
-  const int rb = grid_for(d.cap_active * 64, kWG, 512);
+hipError_t launch_refine_finalize(const Dev &d, const CorrectSpec *corr, const RawSrc *out,
+                                  hipStream_t s) {
+  const int rb = grid_for((out ? out->n_active : d.cap_active) * 64, kWG, 512);
   const dim3 b(kWG);
   const CorrectSpec cs = corr ? *corr : CorrectSpec{};
-  // the corrector's blocks: one thread per active entry
-  const int cb = corr ? grid_for(d.cap_active, kWG, 2048) : 0;
-  if (!corr)
-    hipLaunchKernelGGL((k_ref_final<false, false>), dim3(rb), b, 0, s, d, rb, cs);
+  const ApiOut o = out ? ApiOut{out->acc, out->jerk} : ApiOut{};
+  const int64_t na = out ? out->n_active : 0;
+  // the corrector's or the output's blocks: one thread per active entry
+  const int cb = corr ? grid_for(d.cap_active, kWG, 2048) : (out ? grid_for(na, kWG, 2048) : 0);
+  if (out)
+    hipLaunchKernelGGL((k_ref_final<false, false, true>), dim3(rb + cb), b, 0, s, d, rb, cs, o,
+                       na);
+  else if (!corr)
+    hipLaunchKernelGGL((k_ref_final<false, false, false>), dim3(rb), b, 0, s, d, rb, cs, o, na);
   else if (d.fld.on)
-    hipLaunchKernelGGL((k_ref_final<true, true>), dim3(rb + cb), b, 0, s, d, rb, cs);
+    hipLaunchKernelGGL((k_ref_final<true, true, false>), dim3(rb + cb), b, 0, s, d, rb, cs, o,
+                       na);
   else
-    hipLaunchKernelGGL((k_ref_final<true, false>), dim3(rb + cb), b, 0, s, d, rb, cs);
+    hipLaunchKernelGGL((k_ref_final<true, false, false>), dim3(rb + cb), b, 0, s, d, rb, cs, o,
+                       na);
   return hipGetLastError();
 }
 
@@ -3454,10 +3613,24 @@ hipError_t launch_init_levels(const Dev &d, double eta_start, double dt_shared,
   return hipGetLastError();
 }
 
-hipError_t launch_api_group(const Dev &d, const RawSrc &r, const Tuning &t, hipStream_t s) {
+hipError_t launch_api_group(const Dev &d, const RawSrc &r, hipStream_t s) {
   int64_t need = r.n_active > d.C + 1 ? r.n_active : d.C + 1;
   hipLaunchKernelGGL(k_api_group, dim3((unsigned)((need + kWG - 1) / kWG)),
-                     dim3(kWG), 0, s, d, r.i_active, r.n_active, t, r.n_j);
+                     dim3(kWG), 0, s, d, r.i_active, r.n_active);
+  return hipGetLastError();
+}
+
+hipError_t launch_api_single(const Dev &d, const RawSrc &r, const Tuning &t, bool vref,
+                             const double *eps2, hipStream_t s) {
+  if (vref && !r.v) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_api_single, dim3(1), dim3(kWG), 0, s, d, r, t, vref ? 1 : 0, eps2 ? 1 : 0,
+                     eps2 ? *eps2 : 0.0);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_out(const Dev &d, const RawSrc &r, hipStream_t s) {
+  hipLaunchKernelGGL(k_sum_out, dim3(grid_for(r.n_active * 64, kWG, 4096)), dim3(kWG), 0, s, d,
+                     ApiOut{r.acc, r.jerk});
   return hipGetLastError();
 }
 
