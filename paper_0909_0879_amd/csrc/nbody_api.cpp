@@ -80,6 +80,8 @@ size_t carve(int64_t n, int32_t C, char *base, Dev *d, int rows_per_j = nbk::kRo
   t.blk_cnt = (int32_t *)take(sizeof(int32_t) * t.nblk);
   t.flag_cnt = (int32_t *)take(sizeof(int32_t) * t.nblk);
   t.blk_off = (int32_t *)take(sizeof(int32_t) * (t.nblk + 1));
+  if (nbk::plan_fused(C, t.nblk))
+    t.lvl = (int32_t *)take(sizeof(int32_t) * nbk::kLevels * t.nblk);
   t.plan_c = (nbk::ClusterPlan *)take(sizeof(nbk::ClusterPlan) * C);
   t.plan_lpt = (nbk::ClusterPlan *)take(sizeof(nbk::ClusterPlan) * C);
   t.item_prefix = (int32_t *)take(sizeof(int32_t) * (C + 1));
@@ -411,7 +413,7 @@ Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   if (c->C != 1) return kRouteDevice;
   if (n_j > c->d.n) return kRouteRaw;       // the buffer holds d.n records
   const bool wide = c->tune.i_slots[bucket_of(na)] == nbk::kWG && (acc_only ? c->sba : c->sb);
-  const bool many = wide && na >= nbk::kWG && (acc_only || is_mixed(c->prec));
+  const bool many = wide && na >= (acc_only || is_mixed(c->prec) ? nbk::kWG : 4 * nbk::kWG);
   if (!many && na * 16 < n_j) return kRouteRaw;
   return wide ? kRouteSb : kRouteLds;
 }
@@ -573,11 +575,13 @@ int two_pass(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk::RawS
 int enqueue_block_step(nbody_ctx *c, hipStream_t s) {
   const nbk::Tuning t = device_tuning(c, c->K);
   const bool allow_small = is_mixed(c->prec);
-  const bool rc_records = rec_in_compact(c);
-  NB_HIP(nbk::launch_compact(c->d, t, allow_small, rc_records ? mode_of(c) : -1, c->sb,
-                             rc_records && is_mixed(c->prec) && c->step_sb_only, s));
-  if (!nbk::plan_fused(c->d))
+  if (rec_in_compact(c)) {
+    NB_HIP(nbk::launch_step_head(c->d, t, allow_small, mode_of(c), c->sb,
+                                 is_mixed(c->prec) && c->step_sb_only, s));
+  } else {
+    NB_HIP(nbk::launch_compact(c->d, s));
     NB_HIP(nbk::launch_plan(c->d, t, nbk::kPlanStep, 0, allow_small, s));
+  }
   const nbk::NearSpec nr = near_spec(c, mode_of(c), nbk::kNearState);
   int rc = force_launch(c, mode_of(c), nbk::kSrcState, c->K, nullptr, c->d.active,
                         c->grid_state, s, nbk::kPlanStep, nr);

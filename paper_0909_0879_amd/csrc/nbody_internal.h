@@ -140,6 +140,8 @@ struct Dev {
   int32_t *blk_cnt;    // nblk: due particles per compaction block
   int32_t *flag_cnt;   // nblk: flagged entries per block of the active list
   int32_t *blk_off;    // nblk + 1
+  int32_t *lvl;        // kLevels * nblk, level-major: particles per level and
+                       // compaction block (plan_fused contexts, else null)
   // plan
   ClusterPlan *plan_c;    // C, by cluster id
   ClusterPlan *plan_lpt;  // C, largest item cost first
@@ -224,19 +226,21 @@ hipError_t launch_init_state(const Dev &d, const double *m, const double *x,
                              const double *v, hipStream_t s);
 // Every particle active; with one cluster also the kPlanState plan (tuning t).
 hipError_t launch_all_active(const Dev &d, const Tuning &t, hipStream_t s);
-// One-cluster contexts whose compaction takes its block prefixes itself:
-// the compaction kernels also write the plan that follows (launch_compact
-// the block step's, launch_sum_and_flag the re-evaluation's), and the
-// separate launch_plan is skipped.
+// One-cluster contexts of up to kFusedScan compaction blocks: the kernels that
+// find an active count also write the plan that follows (launch_step_head the
+// block step's, launch_sum_and_flag the re-evaluation's), and the separate
+// launch_plan is skipped.
+constexpr bool plan_fused(int C, int nblk) { return C == 1 && nblk <= kFusedScan; }
 bool plan_fused(const Dev &d);
-// Scheduler (per-cluster T_next and threshold level) and ordered compaction
-// of the due particles into the active list (plan: see plan_fused).
-// rec_mode >= 0 (a force mode; one cluster with plan_fused): the compaction
-// also writes every particle's j record predicted to T_next and the record
-// flag (allow_sb, sb_only as in launch_records), so no launch_records
-// follows; -1: records are left to launch_records.
-hipError_t launch_compact(const Dev &d, const Tuning &t, bool allow_small, int rec_mode,
-                          bool allow_sb, bool sb_only, hipStream_t s);
+// Their block step up to the force launches: scheduler, ordered compaction of
+// the due particles, the records of a step in force mode `mode` and the
+// record flag (allow_sb, sb_only as in launch_records), the plan.
+hipError_t launch_step_head(const Dev &d, const Tuning &t, bool allow_small, int mode,
+                            bool allow_sb, bool sb_only, hipStream_t s);
+// The other contexts' scheduler (per-cluster T_next and threshold level) and
+// ordered compaction of the due particles into the active list; launch_plan
+// and launch_records follow.
+hipError_t launch_compact(const Dev &d, hipStream_t s);
 // allow_small: clusters of a small block step (at most kSmallStep active
 // particles, or at most Tuning::small_work interactions) are planned for the
 // small-step FP64 launch (mixed contexts).  A re-evaluation plan also

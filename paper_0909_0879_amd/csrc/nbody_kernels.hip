@@ -1347,8 +1347,8 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     // all of 2^20 (131072 items) 1554 ms against 1548.  So it needs chunks of
     // 4 kTJ, or too few items to fill the chip (N = 1000: 170 -> 99 us), and
     // is left where the items are many anyway.
-    p.Pt = (P == kWG && tiles * S < kWideItems && (chunk >= 4 * kTJ || tiles * S < kFewItems))
-               ? kBlk : P;
+    const bool share_j = chunk >= 4 * kTJ || tiles * S < kFewItems;
+    p.Pt = (P == kWG && tiles * S < kWideItems && share_j) ? kBlk : P;
     if (p.Pt != P) tiles = (p.na + (int64_t)kBlk * K - 1) / ((int64_t)kBlk * K);
     p.tiles = (int32_t)tiles;
     p.items = (int32_t)(tiles * S);
@@ -1384,8 +1384,7 @@ __device__ void plan_single(const Dev &d, const Tuning &tu, int kind, int64_t ap
   d.work[0] = 0;
   d.work[1] = 0;
   d.work[2] = p.small ? 0 : p.items;
-  if (kind == kPlanStep) {
-    d.T[0] = d.Tnext[0];
+  if (kind == kPlanStep) {       // (the corrector commits T = T_next)
     if (p.items > 0) {
       d.ctr[kCtrInter] += (int64_t)p.na * (p.je - p.jb);
       if (p.small) d.ctr[kCtrSmallInter] += (int64_t)p.na * (p.je - p.jb);
@@ -1497,18 +1496,27 @@ __global__ __launch_bounds__(1024) void k_scan(Dev d, const int32_t *cnt) {
   if (threadIdx.x == 0) d.blk_off[d.nblk] = carry;
 }
 
+// The block's exclusive scan of cnt in thread order (wsum: 4 ints of LDS).
+__device__ __forceinline__ int block_exscan(int cnt, int *wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int incl = cnt;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int wbase = 0;
+  for (int u = 0; u < w; ++u) wbase += wsum[u];
+  return wbase + incl - cnt;
+}
+
 // Ordered compaction: active list ascending in particle index, and each
 // cluster's offset in it.  FUSED: the block sums the counts before it
-// itself (no k_scan).  RMODE >= 0 (one cluster, FUSED, block steps):
-// each block also writes the j records of its particles, predicted to
-// T_next, in place of the record kernel (there one more launch costs more
-// than the prediction), and the plan's thread sets the record flag as the
-// record kernel would (0: not built; 1: built; 2: built and the broadcast
-// kernel takes them, when allow_sb and the cluster's main items have kWG
-// i-slots; with sb_only a flag other than 2 is reported as kErrState).
-template <bool FUSED, int RMODE>
-__global__ __launch_bounds__(kWG) void k_scatter(Dev d, Tuning tu, int plan_kind,
-                                                 int allow_small, int allow_sb, int sb_only) {
+// itself (no k_scan).
+template <bool FUSED>
+__global__ __launch_bounds__(kWG) void k_scatter(Dev d) {
   __shared__ int wsum[4];
   __shared__ int sh4[4];
   const int bpre = FUSED ? block_prefix(d.blk_cnt, blockIdx.x, sh4) : d.blk_off[blockIdx.x];
@@ -1521,19 +1529,7 @@ __global__ __launch_bounds__(kWG) void k_scatter(Dev d, Tuning tu, int plan_kind
     flag[e] = (i < d.n && d.level[i] >= d.Lthr[d.cid[i]]) ? 1 : 0;
     cnt += flag[e];
   }
-  // exclusive scan of cnt over the block, in thread order
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int incl = cnt;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
-  if (lane == 63) wsum[w] = incl;
-  __syncthreads();
-  int wbase = 0;
-  for (int u = 0; u < w; ++u) wbase += wsum[u];
-  int pos = bpre + wbase + incl - cnt;
+  int pos = bpre + block_exscan(cnt, wsum);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int64_t i = base + e;
@@ -1543,56 +1539,120 @@ __global__ __launch_bounds__(kWG) void k_scatter(Dev d, Tuning tu, int plan_kind
       if (flag[e]) d.active[pos++] = (int32_t)i;
     }
   }
-  bool rec_on = false;
-  if constexpr (RMODE >= 0) {
-    // the due count of the whole cluster, for the plan's small-step test
-    // (a step the FP64 small-step launch takes reads no records)
-    __shared__ int sh4t[4];
-    int v = 0;
-    for (int u = threadIdx.x; u < d.nblk; u += kWG) v += d.blk_cnt[u];
-    const int na = block_sum_i(v, sh4t);
-    const bool small = allow_small && tu.small_work >= 0 &&
-                       (na <= kSmallStep || (int64_t)na * d.n <= tu.small_work);
-    // as the record kernel decides: mixed steps always read records, FP64
-    // steps only when at least one particle in 16 is due
-    rec_on = mode_mixed(RMODE) || (int64_t)na * 16 >= d.n;
-    if (d.Lthr[0] != kNoActive && rec_on && !small) {
-      using Rec = typename Traits<RMODE>::Rec;
-      Rec *pred = reinterpret_cast<Rec *>(d.pred);
-      const double mref = mode_mixed(RMODE) ? mass_ref(d.m[0]) : 1.0;
-      const int64_t t1 = d.Tnext[0];
-      double vref[3] = {0.0, 0.0, 0.0};     // the cluster's reference
-      if constexpr (mode_relv(RMODE)) {      // velocity (JRecV form)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) vref[c] = d.vref[c];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t i = (int64_t)blockIdx.x * kScanBlock + e * kWG + threadIdx.x;
-        if (i < d.n) {
-          double xp[3], vp[3];
-          predict_state(d, i, t1, xp, vp);
-          Rec r;
-          make_rec(xp, vp, d.m[i], (int32_t)i, r, mref, vref);
-          pred[i] = r;
-        }
-      }
-    }
-  }
   if (FUSED) {
-    if (blockIdx.x == d.nblk - 1 && threadIdx.x == kWG - 1) {
-      d.act_off[d.C] = pos;
-      // one cluster: the active count is known here, so plan here
-      if (plan_kind >= 0) plan_single(d, tu, plan_kind, 0, allow_small, pos);
-      if constexpr (RMODE >= 0) {
-        const ClusterPlan &p = d.plan_c[0];
-        const bool elig = allow_sb && !(p.na > 0 && !p.small && p.P != kWG);
-        *d.pred_on = rec_on ? (elig ? 2 : 1) : 0;
-        if (sb_only && !(rec_on && elig)) atomicOr(d.err, (int)kErrState);
-      }
-    }
+    if (blockIdx.x == d.nblk - 1 && threadIdx.x == kWG - 1) d.act_off[d.C] = pos;
   } else if (blockIdx.x == 0 && threadIdx.x == 0) {
     d.act_off[d.C] = d.blk_off[d.nblk];
+  }
+}
+
+// Particles per level and compaction block (one cluster; kept up to date by
+// the corrector).
+__global__ __launch_bounds__(kWG) void k_level_table(Dev d) {
+  __shared__ int h[kLevels];
+  if (threadIdx.x < kLevels) h[threadIdx.x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kScanBlock / kWG; ++e) {
+    const int64_t i = (int64_t)blockIdx.x * kScanBlock + e * kWG + threadIdx.x;
+    const int lv = i < d.n ? d.level[i] : -1;
+    if (lv >= 0 && lv < kLevels) atomicAdd(&h[lv], 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < kLevels) d.lvl[threadIdx.x * d.nblk + blockIdx.x] = h[threadIdx.x];
+}
+
+// The head of a one-cluster block step in one launch: T_next and the
+// threshold (every block, from the level histogram), each block's place in
+// the active list (from the level table, so no counting launch goes before),
+// the ordered list, and every particle's j record predicted to T_next when
+// the step reads records.  One more block than the compaction has writes the
+// plan meanwhile (one thread's 3 us, after the list until now) and the record
+// flag, as the record kernel would (0: not built; 1: built; 2: built and the
+// broadcast kernel takes them, when allow_sb and the cluster's main items
+// have kWG i-slots; with sb_only a flag other than 2 is reported as
+// kErrState).  Nothing here writes what another block reads: T moves on in
+// the corrector's launch.  k_count and k_scatter took 4.7 + 7.4 us of a small
+// step at 2^16 and 4.1 + 10.8 us at N = 1024.
+template <int RMODE>
+__global__ __launch_bounds__(kWG) void k_step_head(Dev d, Tuning tu, int allow_small,
+                                                   int allow_sb, int sb_only) {
+  __shared__ int wsum[4];
+  __shared__ int sh4[4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t tend = d.ctr[kCtrTend], T = d.T[0];
+  const int err = *d.err;
+  const uint64_t present = __ballot(lane < kLevels && d.hist[lane < kLevels ? lane : 0] > 0);
+  int64_t tn = T;
+  int L = kNoActive;
+  if (T < tend && err == 0 && present != 0) {
+    const int lmax = 63 - __builtin_clzll(present);
+    const int64_t dtl = (int64_t)1 << (kTickBits - lmax);
+    tn = (T / dtl + 1) * dtl;
+    L = kTickBits - __builtin_ctzll((unsigned long long)tn);
+    if (L < 0) L = 0;
+  }
+  // due particles in the blocks before this one, and in all
+  int before = 0, all = 0;
+  for (int b = tid; b < d.nblk; b += kWG) {
+    int v = 0;
+    for (int l = L; l < kLevels; ++l) v += d.lvl[l * d.nblk + b];
+    all += v;
+    before += b < (int)blockIdx.x ? v : 0;
+  }
+  before = block_sum_i(before, sh4);
+  const int na = block_sum_i(all, sh4);
+  // a step the FP64 small-step launch takes reads no records; mixed steps
+  // otherwise always do, FP64 steps when at least one particle in 16 is due
+  const bool small = allow_small && tu.small_work >= 0 &&
+                     (na <= kSmallStep || (int64_t)na * d.n <= tu.small_work);
+  const bool rec_on = mode_mixed(RMODE) || (int64_t)na * 16 >= d.n;
+  if ((int)blockIdx.x == d.nblk) {
+    if (tid == 0) {
+      d.Tnext[0] = tn;
+      d.Lthr[0] = L;
+      d.act_off[0] = 0;
+      d.act_off[1] = na;
+      plan_single(d, tu, kPlanStep, 0, allow_small, na);
+      const ClusterPlan &p = d.plan_c[0];
+      const bool elig = allow_sb && !(p.na > 0 && !p.small && p.P != kWG);
+      *d.pred_on = rec_on ? (elig ? 2 : 1) : 0;
+      if (sb_only && !(rec_on && elig)) atomicOr(d.err, (int)kErrState);
+    }
+    return;
+  }
+  if (tid == 0) d.flag_cnt[blockIdx.x] = 0;     // this step's flagging pass
+  const int64_t base = (int64_t)blockIdx.x * kScanBlock + tid * 4;
+  int flag[4];
+  int cnt = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    flag[e] = (base + e < d.n && d.level[base + e] >= L) ? 1 : 0;
+    cnt += flag[e];
+  }
+  int pos = before + block_exscan(cnt, wsum);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (flag[e]) d.active[pos++] = (int32_t)(base + e);
+  if (L == kNoActive || !rec_on || small) return;
+  using Rec = typename Traits<RMODE>::Rec;
+  Rec *pred = reinterpret_cast<Rec *>(d.pred);
+  const double mref = mode_mixed(RMODE) ? mass_ref(d.m[0]) : 1.0;
+  double vref[3] = {0.0, 0.0, 0.0};     // the cluster's reference
+  if constexpr (mode_relv(RMODE)) {      // velocity (JRecV form)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) vref[c] = d.vref[c];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int64_t i = (int64_t)blockIdx.x * kScanBlock + e * kWG + tid;
+    if (i < d.n) {
+      double xp[3], vp[3];
+      predict_state(d, i, tn, xp, vp);
+      Rec r;
+      make_rec(xp, vp, d.m[i], (int32_t)i, r, mref, vref);
+      pred[i] = r;
+    }
   }
 }
 
@@ -1958,6 +2018,13 @@ __device__ double ext_pot(const Field &f, const double x[3]) {
   return p;
 }
 
+// A one-cluster block step's time becomes the cluster's (k_step_head leaves it
+// to the corrector's launch, also when nothing was due; k_plan commits the
+// others).
+__device__ __forceinline__ void commit_time(const Dev &d) {
+  if (d.lvl && blockIdx.x == 0 && threadIdx.x == 0) d.T[0] = d.Tnext[0];
+}
+
 // Level changes of one block's corrections: those of cluster c gather in LDS
 // and reach the histogram once per block and level: two same-address atomics
 // per particle, 5.7 ns each, were most of k_ref_final at 2^18 particles due
@@ -1973,7 +2040,12 @@ struct LevelCounts {
     if (threadIdx.x < kLevels) n[threadIdx.x] = 0;
     __syncthreads();
   }
-  __device__ void change(const Dev &d, int cluster, int from, int to) const {
+  __device__ void change(const Dev &d, int64_t i, int cluster, int from, int to) const {
+    if (d.lvl) {                 // one cluster: the compaction's level table
+      const int b = (int)(i / kScanBlock);
+      atomicSub(&d.lvl[from * d.nblk + b], 1);
+      atomicAdd(&d.lvl[to * d.nblk + b], 1);
+    }
     if (cluster == c) {
       atomicSub(&n[from], 1);
       atomicAdd(&n[to], 1);
@@ -2045,7 +2117,7 @@ __device__ __forceinline__ void correct_one(const Dev &d, int64_t i, int c, doub
     const int nl = next_level(lv, dtc, tn, lmin, lmax, fl);
     if (fl) atomicAdd((unsigned long long *)&d.ctr[kCtrFloor], 1ull);
     if (nl != lv) {
-      lc.change(d, c, lv, nl);
+      lc.change(d, i, c, lv, nl);
       d.level[i] = nl;
     }
   }
@@ -2058,6 +2130,7 @@ template <bool FIELD>
 __global__ __launch_bounds__(kWG) void k_sum_correct(Dev d, double eta, double dt_shared,
                                                      int lmin, int lmax) {
   const int lane = threadIdx.x & 63;
+  commit_time(d);
   const int nw = d.sum_prefix[d.C];
   const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
@@ -2657,7 +2730,7 @@ __device__ __forceinline__ bool kick_drift_one(const Dev &d, int64_t i, double c
 // drift and the j record of the evaluation that follows, in one launch (the
 // plan stays: every particle is active in each of them; rec_on: the record
 // flag).  Four launches of about 4 us each before; sixth order at N = 4096:
-// 4.1 -> 3.0 ms for 112 evaluations.
+// 4.13 -> 3.29 ms for 112 evaluations.
 template <bool FIELD>
 __global__ __launch_bounds__(kWG) void k_sum_kick_drift(Dev d, double ck, double cd, int check,
                                                         int rec_on) {
@@ -2946,6 +3019,7 @@ __global__ __launch_bounds__(kWG) void k_ref_final(Dev d, int ref_blocks, Correc
   __shared__ int lh[kLevels];
   LevelCounts lc{lh, -1};
   if constexpr (CORR) {
+    commit_time(d);
     if ((int)blockIdx.x >= ref_blocks) {
       const int na = d.act_off[d.C];
       const int stride = ((int)gridDim.x - ref_blocks) * kWG;
@@ -3172,8 +3246,10 @@ __global__ __launch_bounds__(kWG) void k_set_state1(Dev d, const double *x, cons
     const int lv = level[i];
     const int64_t tk = tick[i];
     d.tick[i] = tk;
-    d.level[i] = lv;
-    if (lv < lmin || lv > lmax || tk < 0) {
+    // a refused level is stored as a valid one: it indexes the level tables
+    const bool ok = lv >= lmin && lv <= lmax && tk >= 0;
+    d.level[i] = ok ? lv : lmax;
+    if (!ok) {
       atomicOr(d.err, kErrState);
       continue;
     }
@@ -3194,7 +3270,6 @@ __global__ void k_set_state2(Dev d) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < d.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int lv = d.level[i];
-    if (lv < 0 || lv >= kLevels) continue;   // already flagged
     const int64_t dt = (int64_t)1 << (kTickBits - lv);
     const int64_t tk = d.tick[i];
     const int64_t T = d.T[d.cid[i]];
@@ -3254,33 +3329,31 @@ hipError_t launch_all_active(const Dev &d, const Tuning &t, hipStream_t s) {
   return hipGetLastError();
 }
 
-bool plan_fused(const Dev &d) { return d.C == 1 && d.nblk <= kFusedScan; }
+bool plan_fused(const Dev &d) { return plan_fused(d.C, d.nblk); }
 
-hipError_t launch_compact(const Dev &d, const Tuning &t, bool allow_small, int rec_mode,
-                          bool allow_sb, bool sb_only, hipStream_t s) {
-  hipLaunchKernelGGL(k_count, dim3(d.nblk), dim3(kWG), 0, s, d);
+hipError_t launch_step_head(const Dev &d, const Tuning &t, bool allow_small, int mode,
+                            bool allow_sb, bool sb_only, hipStream_t s) {
+  if (!d.lvl) return hipErrorInvalidValue;
+  const dim3 g(d.nblk + 1), b(kWG);
   const int al = allow_small ? 1 : 0, sb = allow_sb ? 1 : 0, so = sb_only ? 1 : 0;
+  if (mode == kModeFP64)
+    hipLaunchKernelGGL(k_step_head<kModeFP64>, g, b, 0, s, d, t, al, sb, so);
+  else if (mode == kModeMixed64)
+    hipLaunchKernelGGL(k_step_head<kModeMixed64>, g, b, 0, s, d, t, al, sb, so);
+  else if (mode == kModeMixed)
+    hipLaunchKernelGGL(k_step_head<kModeMixed>, g, b, 0, s, d, t, al, sb, so);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_compact(const Dev &d, hipStream_t s) {
+  hipLaunchKernelGGL(k_count, dim3(d.nblk), dim3(kWG), 0, s, d);
   if (d.nblk <= kFusedScan) {
-    const int pk = plan_fused(d) ? (int)kPlanStep : -1;
-    if (rec_mode >= 0 && !plan_fused(d))
-      return hipErrorInvalidValue;
-    if (rec_mode == kModeFP64)
-      hipLaunchKernelGGL((k_scatter<true, kModeFP64>), dim3(d.nblk), dim3(kWG), 0, s, d, t, pk,
-                         al, sb, so);
-    else if (rec_mode == kModeMixed64)
-      hipLaunchKernelGGL((k_scatter<true, kModeMixed64>), dim3(d.nblk), dim3(kWG), 0, s, d, t,
-                         pk, al, sb, so);
-    else if (rec_mode == kModeMixed)
-      hipLaunchKernelGGL((k_scatter<true, kModeMixed>), dim3(d.nblk), dim3(kWG), 0, s, d, t, pk,
-                         al, sb, so);
-    else
-      hipLaunchKernelGGL((k_scatter<true, -1>), dim3(d.nblk), dim3(kWG), 0, s, d, t, pk, al, sb,
-                         so);
+    hipLaunchKernelGGL(k_scatter<true>, dim3(d.nblk), dim3(kWG), 0, s, d);
   } else {
-    if (rec_mode >= 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, d, (const int32_t *)d.blk_cnt);
-    hipLaunchKernelGGL((k_scatter<false, -1>), dim3(d.nblk), dim3(kWG), 0, s, d, t, -1, al, sb,
-                       so);
+    hipLaunchKernelGGL(k_scatter<false>, dim3(d.nblk), dim3(kWG), 0, s, d);
   }
   return hipGetLastError();
 }
@@ -3610,6 +3683,7 @@ hipError_t launch_init_levels(const Dev &d, double eta_start, double dt_shared,
   else
     hipLaunchKernelGGL(k_init_levels<false>, g, dim3(kWG), 0, s, d, eta_start, dt_shared,
                        level_min, level_max);
+  if (d.lvl) hipLaunchKernelGGL(k_level_table, dim3(d.nblk), dim3(kWG), 0, s, d);
   return hipGetLastError();
 }
 
@@ -3686,6 +3760,7 @@ hipError_t launch_set_state(const Dev &d, const double *x, const double *v,
                      x, v, a, jk, tick, level, level_min, level_max, per);
   int64_t need = d.n > d.C ? d.n : d.C;
   hipLaunchKernelGGL(k_set_state2, dim3(grid_for(need)), dim3(kWG), 0, s, d);
+  if (d.lvl) hipLaunchKernelGGL(k_level_table, dim3(d.nblk), dim3(kWG), 0, s, d);
   return hipGetLastError();
 }
 
