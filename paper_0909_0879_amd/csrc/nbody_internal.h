@@ -177,7 +177,8 @@ struct Dev {
 // caller's arrays, or only the records (launches that always have them).
 enum Source : int { kSrcState = 0, kSrcRaw = 1, kSrcRec = 2 };
 // What the force kernel computes: acceleration and jerk, the potential, or
-// the acceleration alone (the symplectic drivers and nbody_accel); in FP64,
+// the acceleration alone (the symplectic drivers and nbody_accel), or the jerk
+// alone (the first pass of a two-pass mixed evaluation); in FP64,
 // mixed with double-single differences, or mixed with FP64 differences.
 enum Mode : int {
   kModeFP64 = 0,
@@ -186,15 +187,19 @@ enum Mode : int {
   kModeFP64Acc = 3,
   kModeMixedAcc = 4,
   kModeMixed64 = 5,
-  kModeMixed64Acc = 6
+  kModeMixed64Acc = 6,
+  kModeMixedJerk = 7,
+  kModeMixed64Jerk = 8
 };
 constexpr bool mode_acc_only(int m) {
   return m == kModeFP64Acc || m == kModeMixedAcc || m == kModeMixed64Acc;
 }
+constexpr bool mode_jerk_only(int m) { return m == kModeMixedJerk || m == kModeMixed64Jerk; }
 // FP32 pair arithmetic: compensated FP32 sums, the largest-term bound and
 // the FP64 re-evaluation
 constexpr bool mode_mixed(int m) {
-  return m == kModeMixed || m == kModeMixedAcc || m == kModeMixed64 || m == kModeMixed64Acc;
+  return m == kModeMixed || m == kModeMixedAcc || m == kModeMixed64 || m == kModeMixed64Acc ||
+         mode_jerk_only(m);
 }
 
 // Near pairs of the mixed evaluations with jerk (evaluated in FP64, left out

@@ -496,6 +496,49 @@ __device__ __forceinline__ uint64_t pair_mixed64_acc(const IV &I, int iidx, cons
   return 0;
 }
 
+// Jerk only, the first pass of an evaluation that has no jerk estimate: the
+// operations of pair_mixed / pair_mixed64 on the way to the jerk sums (so the
+// thresholds are those of a full pass without near pairs), without the
+// acceleration, the largest-term bound and the near-pair test.
+template <bool MASK, bool SELF, class I_, class R_>
+__device__ __forceinline__ void pair_jerk(const I_ &I, int iidx, const R_ &r, float eps2, float dx,
+                                          float dy, float dz, float wx, float wy, float wz,
+                                          float m, float *t, int &dom) {
+  (void)I;
+  const float s = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
+  const float rv = fmaf(dx, wx, fmaf(dy, wy, dz * wz));
+  float r0 = __builtin_amdgcn_rsqf(s);
+  if (MASK) {
+    if (dx == 0.0f && dy == 0.0f && dz == 0.0f) {
+      r0 = 0.0f;
+      dom |= (r.idx != iidx);
+    }
+  }
+  const Fac32 f = fac32(s, m, r0);
+  const float al = (3.0f * rv) * f.rinv2;
+  const float mr3 = (SELF && r.idx == iidx) ? 0.0f : f.mr3;
+  t[0] = fmaf(mr3, fmaf(-al, dx, wx), t[0]);
+  t[1] = fmaf(mr3, fmaf(-al, dy, wy), t[1]);
+  t[2] = fmaf(mr3, fmaf(-al, dz, wz), t[2]);
+}
+
+template <bool MASK, bool SELF>
+__device__ __forceinline__ void pair_mixed_jerk(const IDS &I, int iidx, const JRecDS &r,
+                                                float eps2, float *t, int &dom) {
+  pair_jerk<MASK, SELF>(I, iidx, r, eps2, (r.xh - I.xh[0]) + (r.xl - I.xl[0]),
+                        (r.yh - I.xh[1]) + (r.yl - I.xl[1]), (r.zh - I.xh[2]) + (r.zl - I.xl[2]),
+                        (r.vx - I.v[0]) + (r.vlx - I.vl[0]), (r.vy - I.v[1]) + (r.vly - I.vl[1]),
+                        (r.vz - I.v[2]) + (r.vlz - I.vl[2]), r.m, t, dom);
+}
+
+template <bool MASK, bool SELF>
+__device__ __forceinline__ void pair_mixed64_jerk(const IV &I, int iidx, const JRecV &r,
+                                                  float eps2, float *t, int &dom) {
+  pair_jerk<MASK, SELF>(I, iidx, r, eps2, (float)(r.x - I.x[0]), (float)(r.y - I.x[1]),
+                        (float)(r.z - I.x[2]), (r.vx - I.vh[0]) - I.vl[0],
+                        (r.vy - I.vh[1]) - I.vl[1], (r.vz - I.vh[2]) - I.vl[2], r.mf, t, dom);
+}
+
 // The FP64 term of a near pair (pair_fp64's arithmetic on the FP64 predicted
 // states), added to the compensated FP32 sums: each component as the FP32
 // pair hi = T rounded, lo = (T - hi) rounded, hi through TwoSum into
@@ -577,6 +620,20 @@ template <> struct Traits<kModeMixed64Acc> {
   static constexpr int NC = 3;
   static constexpr int FOLD = 1;
 };
+template <> struct Traits<kModeMixedJerk> {
+  using T = float;
+  using Rec = JRecDS;
+  using Ist = IDS;
+  static constexpr int NC = 3;
+  static constexpr int FOLD = 1;
+};
+template <> struct Traits<kModeMixed64Jerk> {
+  using T = float;
+  using Rec = JRecV;
+  using Ist = IV;
+  static constexpr int NC = 3;
+  static constexpr int FOLD = 1;
+};
 template <> struct Traits<kModePot> {
   using T = double;
   using Rec = JRec64;
@@ -603,7 +660,11 @@ __device__ __forceinline__ void fold(typename Traits<MODE>::T (&t)[K][Traits<MOD
 constexpr bool mode_near(int m) { return m == kModeMixed || m == kModeMixed64; }
 // Modes whose records hold velocities relative to the cluster's reference
 // velocity (JRecV).
-constexpr bool mode_relv(int m) { return m == kModeMixed64 || m == kModeMixed64Acc; }
+constexpr bool mode_relv(int m) {
+  return m == kModeMixed64 || m == kModeMixed64Acc || m == kModeMixed64Jerk;
+}
+// First column of a partial row that a mode's sums fill.
+constexpr int mode_col(int m) { return mode_jerk_only(m) ? 3 : 0; }
 
 // One j record against the K i-particles of a lane; nr[k] is the wave's lane
 // mask of near pairs with i-particle k (left out of the FP32 sums, see
@@ -628,6 +689,10 @@ __device__ __forceinline__ void pair_k(const typename Traits<MODE>::Rec &r,
       pair_fp64_acc<MASK>(I[k], iidx[k], r, eps2, t[k], dom[k]);
     else if constexpr (MODE == kModeMixed64)
       nr[k] = pair_mixed64<MASK, SELF>(I[k], iidx[k], r, (float)eps2, th[k], t[k], dom[k], ba[k]);
+    else if constexpr (MODE == kModeMixedJerk)
+      pair_mixed_jerk<MASK, SELF>(I[k], iidx[k], r, (float)eps2, t[k], dom[k]);
+    else if constexpr (MODE == kModeMixed64Jerk)
+      pair_mixed64_jerk<MASK, SELF>(I[k], iidx[k], r, (float)eps2, t[k], dom[k]);
     else if constexpr (MODE == kModeMixed64Acc)
       pair_mixed64_acc<MASK, SELF>(I[k], iidx[k], r, (float)eps2, th[k], t[k], dom[k], ba[k]);
     else
@@ -1113,10 +1178,10 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
         if (slot < cp.na) {
           double *row = d.partial + (cp.row_off + (int64_t)split * cp.na + slot) * kRowStride;
 #pragma unroll
-          for (int c = 0; c < NC; ++c) row[c] = ok[k] ? res[k][c] : 0.0;
+          for (int c = 0; c < NC; ++c) row[mode_col(MODE) + c] = ok[k] ? res[k][c] : 0.0;
           if (MODE != kModePot) {
 #pragma unroll
-            for (int c = NC; c < 6; ++c) row[c] = 0.0;    // no jerk in acc-only modes
+            for (int c = NC; c < 6; ++c) row[c - mode_col(MODE)] = 0.0;   // the other half
             if (ba[k].near > kNearQ) ba[k].a = INFINITY;
             row[6] = ok[k] ? (double)ba[k].a * mref : 0.0;
             row[7] = ok[k] ? (double)ba[k].f1 * mref : 0.0;
@@ -2466,7 +2531,7 @@ __device__ __forceinline__ void sb_run(
   // FP64 417 -> 398 us at 5000 of 65536).  The double-single loop, whose
   // scheduler does neither, runs out of vector registers that way (7.60 ->
   // 8.70 ms).
-  constexpr bool fence = MODE != kModeMixed;
+  constexpr bool fence = MODE != kModeMixed && MODE != kModeMixedJerk;
   int jj = 0;
   Rec first = load_rec(rec);
   for (; jj + G <= cnt; jj += G) {
@@ -2659,9 +2724,9 @@ __attribute__((amdgpu_waves_per_eu(SbOcc<MODE, K>::waves))) void k_force_sb(Forc
         if (slot < cp.na) {
           double *row = d.partial + (cp.row_off + (int64_t)split * cp.na + slot) * kRowStride;
 #pragma unroll
-          for (int c = 0; c < NC; ++c) row[c] = ok[k] ? res[k][c] : 0.0;
+          for (int c = 0; c < NC; ++c) row[mode_col(MODE) + c] = ok[k] ? res[k][c] : 0.0;
 #pragma unroll
-          for (int c = NC; c < 6; ++c) row[c] = 0.0;
+          for (int c = NC; c < 6; ++c) row[c - mode_col(MODE)] = 0.0;
           if (ba[k].near > kNearQ) ba[k].a = INFINITY;
           row[6] = ok[k] ? (double)ba[k].a * mref : 0.0;
           row[7] = ok[k] ? (double)ba[k].f1 * mref : 0.0;
@@ -3430,6 +3495,14 @@ hipError_t launch_force(const Dev &d, int mode, int src, int K,
   NB_CASE(kModeMixed64Acc, kSrcRaw, 2)
   NB_CASE(kModeMixed64Acc, kSrcRec, 1)
   NB_CASE(kModeMixed64Acc, kSrcRec, 2)
+  NB_CASE(kModeMixedJerk, kSrcRaw, 1)
+  NB_CASE(kModeMixedJerk, kSrcRaw, 2)
+  NB_CASE(kModeMixedJerk, kSrcRec, 1)
+  NB_CASE(kModeMixedJerk, kSrcRec, 2)
+  NB_CASE(kModeMixed64Jerk, kSrcRaw, 1)
+  NB_CASE(kModeMixed64Jerk, kSrcRaw, 2)
+  NB_CASE(kModeMixed64Jerk, kSrcRec, 1)
+  NB_CASE(kModeMixed64Jerk, kSrcRec, 2)
   NB_CASE(kModePot, kSrcState, 1)
 #undef NB_CASE
   return hipErrorInvalidValue;
@@ -3474,6 +3547,14 @@ int force_grid_size(int mode, int src, int K, int device) {
   NB_CASE(kModeMixed64Acc, kSrcRaw, 2)
   NB_CASE(kModeMixed64Acc, kSrcRec, 1)
   NB_CASE(kModeMixed64Acc, kSrcRec, 2)
+  NB_CASE(kModeMixedJerk, kSrcRaw, 1)
+  NB_CASE(kModeMixedJerk, kSrcRaw, 2)
+  NB_CASE(kModeMixedJerk, kSrcRec, 1)
+  NB_CASE(kModeMixedJerk, kSrcRec, 2)
+  NB_CASE(kModeMixed64Jerk, kSrcRaw, 1)
+  NB_CASE(kModeMixed64Jerk, kSrcRaw, 2)
+  NB_CASE(kModeMixed64Jerk, kSrcRec, 1)
+  NB_CASE(kModeMixed64Jerk, kSrcRec, 2)
   NB_CASE(kModePot, kSrcState, 1)
 #undef NB_CASE
   return 0;
@@ -3533,9 +3614,10 @@ hipError_t launch_records(const Dev &d, int mode, int kind, const RawSrc *raw,
   const int64_t nj = (kind == kPlanApi && r.n_j > 0) ? r.n_j : d.n;
   const dim3 g(grid_for(nj, kWG, 1024)), b(kWG);
   const int sb = allow_sb ? 1 : 0, al = always ? 1 : 0, so = sb_only ? 1 : 0;
-  if (mode == kModeMixed || mode == kModeMixedAcc)     // double-single records
+  if (mode == kModeMixed || mode == kModeMixedAcc || mode == kModeMixedJerk)   // double-single
     hipLaunchKernelGGL(k_records<kModeMixed>, g, b, 0, s, d, kind, r, sb, al, so);
-  else if (mode == kModeMixed64 || mode == kModeMixed64Acc)   // FP64 records, m / m_ref
+  else if (mode == kModeMixed64 || mode == kModeMixed64Acc ||
+           mode == kModeMixed64Jerk)                  // FP64 positions, m / m_ref
     hipLaunchKernelGGL(k_records<kModeMixed64>, g, b, 0, s, d, kind, r, sb, al, so);
   else
     hipLaunchKernelGGL(k_records<kModeFP64>, g, b, 0, s, d, kind, r, sb, al, so);
@@ -3569,6 +3651,10 @@ hipError_t launch_force_sb(const Dev &d, int mode, int K, const RawSrc *raw,
   NB_CASE(kModeMixed64, 2)
   NB_CASE(kModeMixed64Acc, 1)
   NB_CASE(kModeMixed64Acc, 2)
+  NB_CASE(kModeMixedJerk, 1)
+  NB_CASE(kModeMixedJerk, 2)
+  NB_CASE(kModeMixed64Jerk, 1)
+  NB_CASE(kModeMixed64Jerk, 2)
 #undef NB_CASE
   return hipErrorInvalidValue;
 }
@@ -3589,6 +3675,10 @@ int force_sb_grid_size(int mode, int K, int device) {
   NB_CASE(kModeMixed64, 2)
   NB_CASE(kModeMixed64Acc, 1)
   NB_CASE(kModeMixed64Acc, 2)
+  NB_CASE(kModeMixedJerk, 1)
+  NB_CASE(kModeMixedJerk, 2)
+  NB_CASE(kModeMixed64Jerk, 1)
+  NB_CASE(kModeMixed64Jerk, 2)
 #undef NB_CASE
   if (!f) return 0;
   int per_cu = 0, cus = 0;
