@@ -428,6 +428,9 @@ Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   const bool wide = c->tune.i_slots[bucket_of(na)] == nbk::kWG && (acc_only ? c->sba : c->sb);
   const bool many = wide && na >= (acc_only || is_mixed(c->prec) ? nbk::kWG : 4 * nbk::kWG);
   if (!many && na * 16 < n_j) return kRouteRaw;
+  // small systems: the record launch costs more than converting in the fill
+  // (N = 1024, every particle: 23 -> 20 us a call)
+  if (!wide && na * n_j <= ((int64_t)1 << 22)) return kRouteRaw;
   return wide ? kRouteSb : kRouteLds;
 }
 
