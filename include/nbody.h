@@ -298,15 +298,20 @@ const char *nbody_last_error(void);
  * cluster with n_active particles in bucket b = floor(log2(n_active))
  * (0..24), i_slots[b] threads of a 256-thread workgroup hold i-particles
  * (a power of two, 1..256; the other 256 / i_slots lanes split j inside the
- * workgroup) and the j range is split until the cluster has about
+ * workgroup; 256 is a wide item, which holds 256 i-particles, or 64 whose four
+ * waves split j where its j range is long or the items are few) and the j
+ * range is split until the cluster has about
  * target_items[b] items (1..2^20), within two bounds: no split shorter than
- * min_split_j, and splits x n_active <= 32 n_j (the partial-sum rows the
+ * min_split_j (wide items of FP64 and acceleration-only evaluations: than 1024
+ * where that leaves enough items), and splits x n_active <= 32 n_j (the partial-sum rows the
  * workspace holds per j-particle).  variant selects the compiled kernel shape:
  * NBODY_VARIANT_K1 (one i per thread slot) or NBODY_VARIANT_K2 (two), both
  * staging j through LDS; NBODY_VARIANT_S1 / _S2 add the broadcast kernel
  * (j records read into scalar registers) for evaluations with at least
  * n_j / 16 active particles and i_slots = 256 in every cluster, with one or
- * two i per lane (the LDS kernel with the same K takes the others).  All
+ * two i per lane (the LDS kernel with the same K takes the others;
+ * nbody_forces and nbody_accel of one cluster use it from 256 entries on in
+ * the mixed forms and acceleration-only, from 1024 in FP64).  All
  * variants with the same K give bitwise-identical results.
  * Zero fields keep the defaults. */
 #define NBODY_TUNE_BUCKETS 25

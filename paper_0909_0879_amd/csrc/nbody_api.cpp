@@ -420,8 +420,9 @@ Route state_route(const nbody_ctx *c, bool acc_only) {
 // Route of na entries against n_j caller's particles.  Records pay when each
 // is read by many i: from one entry in 16 on, and, where the broadcast kernel
 // takes them, from one wide item's worth of entries on in the mixed forms and
-// the acceleration-only ones (1001 of 262144 mixed, two passes: 570 -> 430 us;
-// the tile fill converts each j again for every 64 or 256 entries).
+// the acceleration-only ones (1001 of 262144 mixed, two passes: 570 -> 552 us
+// with the item shapes and the jerk-only first pass in; the tile fill converts
+// each j again for every 64 or 256 entries).
 Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   if (c->C != 1) return kRouteDevice;
   if (n_j > c->d.n) return kRouteRaw;       // the buffer holds d.n records
@@ -429,7 +430,7 @@ Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   const bool many = wide && na >= (acc_only || is_mixed(c->prec) ? nbk::kWG : 4 * nbk::kWG);
   if (!many && na * 16 < n_j) return kRouteRaw;
   // small systems: the record launch costs more than converting in the fill
-  // (N = 1024, every particle: 23 -> 20 us a call)
+  // (N = 1024, every particle: 23 -> 18 us a call)
   if (!wide && na * n_j <= ((int64_t)1 << 22)) return kRouteRaw;
   return wide ? kRouteSb : kRouteLds;
 }
@@ -575,7 +576,7 @@ int sum_and_refine(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk
 // mode, told whether it is the first (the plan and the records stay valid; the
 // sums in between reset the item counters).  The first of two passes sums the
 // jerk alone: 32 instead of 40 instructions a pair (all of 2^16, mixed: 6.54
-// -> 6.1 ms for both).
+// -> 6.04 ms for both).
 template <class F>
 int two_pass(nbody_ctx *c, const int32_t *list, int64_t na_host, const nbk::RawSrc *raw,
              hipStream_t s, int mode, F launch) {

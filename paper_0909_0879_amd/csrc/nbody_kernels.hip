@@ -1373,8 +1373,7 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     P = 1 << (31 - __builtin_clz((unsigned)P));      // power of two
     p.P = P;
     // 32-bit counts (n <= 2^30) and shifts: one thread plans, and a 64-bit
-    // division is 150 instructions of its chain (seven of them: 18.4 -> 17.8
-    // us for N = 1024 without a context, 256 clusters 1 % of a step)
+    // division is 150 instructions of its chain
     const uint32_t una = (uint32_t)p.na, unc = (uint32_t)nc;
     const int ilog = 31 - __builtin_clz((unsigned)(P * K));     // K is 1 or 2
     int64_t tiles = (una + (1u << ilog) - 1) >> ilog;
