@@ -165,7 +165,9 @@ struct Dev {
   double *vref;        // 3 * C: each cluster's reference velocity of the
                        // FP64-difference mixed records (k_vref)
   int32_t *sync;       // [0] flagged-entry count, [1] finished blocks of an
-                       // appending k_sum_flag (both zero between launches)
+                       // appending k_sum_flag (both zero between launches),
+                       // [2] row-sum waves of the block step's plan, which
+                       // the re-evaluation's plan leaves alone
   int32_t *err;        // sticky error bits
   int64_t *ctr;        // kCtrCount counters
   double *eout;        // C * 9 energy output

@@ -1452,6 +1452,7 @@ __device__ void plan_single(const Dev &d, const Tuning &tu, int kind, int64_t ap
   d.work[1] = 0;
   d.work[2] = p.small ? 0 : p.items;
   if (kind == kPlanStep) {       // (the corrector commits T = T_next)
+    d.sync[2] = sum_waves(p);
     if (p.items > 0) {
       d.ctr[kCtrInter] += (int64_t)p.na * (p.je - p.jb);
       if (p.small) d.ctr[kCtrSmallInter] += (int64_t)p.na * (p.je - p.jb);
@@ -2914,7 +2915,11 @@ __global__ void k_sym_advance(Dev d, int64_t dticks) {
 // re-evaluation list through one atomic counter, in whatever order they
 // come (each entry's FP64 sums do not depend on its place in the list), and
 // the last of the blocks that own work waves to finish publishes the count
-// and writes the re-evaluation plan (plan_kind), in place of k_rscatter.
+// and writes the re-evaluation plan (plan_kind), in place of k_rscatter.  A
+// block may start after that, and the new plan can hold more waves than the
+// old one (its lanes per entry are capped apart): the wave count is therefore
+// read from a word of the step's own plan, and only blocks that still owe a
+// ticket read the plan itself.
 template <bool APPEND>
 __global__ __launch_bounds__(kWG) void k_sum_flag(Dev d, const int32_t *list, float ratio,
                                                   float near_c, int near_src, int theta_out,
@@ -2922,7 +2927,7 @@ __global__ __launch_bounds__(kWG) void k_sum_flag(Dev d, const int32_t *list, fl
   const int lane = threadIdx.x & 63;
   // the second pass of the same plan counts its items from zero
   if (theta_out && blockIdx.x == 0 && threadIdx.x < 2) d.work[threadIdx.x] = 0;
-  const int nw = d.sum_prefix[d.C];
+  const int nw = APPEND ? d.sync[2] : d.sum_prefix[d.C];
   const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
   extern __shared__ int32_t s_spre[];   // sum_prefix when prefix_in_lds(C)
