@@ -583,7 +583,8 @@ template <int MODE> struct Traits {          // FP64 forces
   using Rec = JRec64;
   using Ist = I64;
   static constexpr int NC = 6;
-  static constexpr int FOLD = 4;             // tiles of kTJ j per compensated fold
+  static constexpr int FOLD = 4;             // blocks of kBlk j per compensated fold
+                                             // (wide items; others fold every tile)
 };
 template <> struct Traits<kModeMixed> {
   using T = float;
@@ -1140,8 +1141,12 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
           tile_loop<MODE, K, false, false>(rb, bc, q0, step, I, iidx, eps2, th, t, dom, ba, ncnt, nq);
         if (Tr::FOLD == 1) fold<MODE, K>(t, shi, slo);
       }
-      if (Tr::FOLD > 1 &&
-          ((++tiles & (Tr::FOLD - 1)) == 0 || Pt == kWG || jt + kTJ >= je))
+      // FP64 forms: every tile, except where a lane of a shared-j item meets
+      // only kBlk records of each (four tiles make its kTJ terms; a narrow
+      // item's lane, which meets as few, folds them by the tile all the same:
+      // its sums over four tiles are four times as far off)
+      if (Tr::FOLD > 1 && (!wide || Pt == kWG || (++tiles & (Tr::FOLD - 1)) == 0 ||
+                           jt + kTJ >= je))
         fold<MODE, K>(t, shi, slo);
       __syncthreads();
     }
