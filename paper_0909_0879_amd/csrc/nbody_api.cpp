@@ -3,6 +3,7 @@
 // the contract of every entry point.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -228,12 +229,16 @@ nbody_tuning default_tuning(int precision) {
     t.target_items[b] = b >= 16 ? 131072 : 2048;
     if (precision == NBODY_FP64) {
       // as many slots as particles up to one wave, wide items from 2^11 on
-      // (N = 1024, every particle: 27 us a call where 256 slots, 8
-      // workgroups, took 73); about 2048 items from 64 particles on, 16 to
-      // 32 j-splits of a full evaluation (N = 2^14: 16 splits 301 us, 8 320,
-      // 32 311)
+      // (N = 1024, every particle, in nine launches a call: 27 us where 256
+      // slots, 8 workgroups, took 73; in today's three launches 18); about
+      // 2048 items from 64 particles on, 16 to 32 j-splits of a full
+      // evaluation (N = 2^14: 16 splits 301 us, 8 320, 32 311), and no more
+      // items than nbody_set_tuning accepts
       t.i_slots[b] = b < 6 ? 1 << b : (b < 11 ? 64 : 256);
-      t.target_items[b] = b < 6 ? 512 : b < 11 ? 2048 : b < 12 ? 512 : 1 << (b < 16 ? b - 2 : b - 3);
+      t.target_items[b] = b < 6    ? 512
+                          : b < 11 ? 2048
+                          : b < 12 ? 512
+                                   : 1 << std::min(b < 16 ? b - 2 : b - 3, 20);
     }
   }
   return t;
