@@ -2887,10 +2887,13 @@ __global__ void k_sym_kick(Dev d, double ck) {
   }
 }
 
-// Advance every particle's and cluster's time by dticks.
+// Advance every particle's and cluster's time by dticks, and clear the level
+// histogram: the evaluation that follows chooses every level anew.
 __global__ void k_sym_advance(Dev d, int64_t dticks) {
   const int64_t gt = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (int64_t i = gt; i < d.n; i += (int64_t)gridDim.x * blockDim.x) d.tick[i] += dticks;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = gt; i < d.n; i += stride) d.tick[i] += dticks;
+  for (int64_t i = gt; i < (int64_t)d.C * kLevels; i += stride) d.hist[i] = 0;
   if (gt < d.C) {
     d.T[gt] += dticks;
     d.Tnext[gt] = d.T[gt];
