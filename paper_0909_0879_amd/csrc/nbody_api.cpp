@@ -424,15 +424,21 @@ Route state_route(const nbody_ctx *c, bool acc_only) {
 
 // Route of na entries against n_j caller's particles.  Records pay when each
 // is read by many i: from one entry in 16 on, and, where the broadcast kernel
-// takes them, from one wide item's worth of entries on in the mixed forms and
-// the acceleration-only ones (1001 of 262144 mixed, two passes: 570 -> 552 us
-// with the item shapes and the jerk-only first pass in; the tile fill converts
-// each j again for every 64 or 256 entries).
+// takes them, from fewer.  With jerk in FP64 from four wide items' worth on
+// (3000 of 2^16: 252 us broadcast, 262 with the tile fill).  Elsewhere the tile
+// fill converts a j so cheaply that it takes eight of them and enough pairs to
+// carry the record launch: mixed 1001 of 2^18 522 us filled against 553, 2100
+// of it 1058 against 976; double-single, acceleration only, 2100 of 2^16 116
+// against 140; the other two, acceleration only, from half as many pairs
+// (mixed 2100 of 2^17 202 against 196, 3000 of 2^16 141 against 152).
 Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   if (c->C != 1) return kRouteDevice;
   if (n_j > c->d.n) return kRouteRaw;       // the buffer holds d.n records
   const bool wide = c->tune.i_slots[bucket_of(na)] == nbk::kWG && (acc_only ? c->sba : c->sb);
-  const bool many = wide && na >= (acc_only || is_mixed(c->prec) ? nbk::kWG : 4 * nbk::kWG);
+  const int64_t pairs = (int64_t)1 << (acc_only && c->prec != NBODY_MIXED_DS ? 28 : 29);
+  const bool many = wide && (acc_only || is_mixed(c->prec)
+                                 ? na >= 8 * nbk::kWG && na * n_j >= pairs
+                                 : na >= 4 * nbk::kWG);
   if (!many && na * 16 < n_j) return kRouteRaw;
   // small systems: the record launch costs more than converting in the fill
   // (N = 1024, every particle: 23 -> 18 us a call)
