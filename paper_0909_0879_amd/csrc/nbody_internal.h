@@ -13,7 +13,7 @@ constexpr int kWG = 256;            // threads per workgroup of every kernel
 constexpr int kTJ = 256;            // j records per LDS tile of the force kernel
 constexpr int kBlk = 64;            // j per block of a wide item, and the
                                     // i-slots of one whose waves share j
-constexpr int kFewItems = 256;      // fewer items of kWG slots than CUs: they
+constexpr int kFewItems = 256;      // up to one item of kWG slots a CU: they
                                     // are cut into four whatever their length
 constexpr int64_t kWideItems = 65536;   // from this many items of kWG slots on
                                     // the waves of a wide item share i instead

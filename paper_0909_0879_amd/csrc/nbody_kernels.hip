@@ -1417,9 +1417,10 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     // the scalar cache and pays an item's start and end on a quarter of the
     // pairs: with 256-record chunks all of 2^14 took 703 us against 568, and
     // all of 2^20 (131072 items) 1554 ms against 1548.  So it needs chunks of
-    // 4 kTJ, or too few items to fill the chip (N = 1000: 170 -> 99 us), and
-    // is left where the items are many anyway.
-    const bool share_j = chunk >= 4 * kTJ || tiles * S < kFewItems;
+    // 4 kTJ, or too few items to fill the chip (N = 1000: 170 -> 99 us; N =
+    // 4096, one item a CU, double-single: 151 -> 139 us, acceleration only 66
+    // -> 57), and is left where the items are many anyway.
+    const bool share_j = chunk >= 4 * kTJ || tiles * S <= kFewItems;
     p.Pt = (P == kWG && tiles * S < kWideItems && share_j) ? kBlk : P;
     if (p.Pt != P) tiles = (una + (uint32_t)(kBlk * K) - 1) / (uint32_t)(kBlk * K);
     p.tiles = (int32_t)tiles;
