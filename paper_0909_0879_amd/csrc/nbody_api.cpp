@@ -231,13 +231,16 @@ nbody_tuning default_tuning(int precision) {
       // as many slots as particles up to one wave, wide items from 2^11 on
       // (N = 1024, every particle, in nine launches a call: 27 us where 256
       // slots, 8 workgroups, took 73; in today's three launches 18); about
-      // 2048 items from 64 particles on, 16 to 32 j-splits of a full
-      // evaluation (N = 2^14: 16 splits 301 us, 8 320, 32 311), and no more
-      // items than nbody_set_tuning accepts
+      // 2048 items from 64 particles on, and 4096 of wide ones, so that a last
+      // round of them costs little (3000 of 2^18: with 512 items of 256 slots,
+      // 2021 of 64, 921 us a call, acceleration only 632; with 4096 844 and
+      // 516); from 2^14 particles on 16 to 32 j-splits of a full evaluation
+      // (2^14: 16 splits 301 us, 8 320, 32 311), and no more items than
+      // nbody_set_tuning accepts
       t.i_slots[b] = b < 6 ? 1 << b : (b < 11 ? 64 : 256);
       t.target_items[b] = b < 6    ? 512
                           : b < 11 ? 2048
-                          : b < 12 ? 512
+                          : b < 14 ? 4096
                                    : 1 << std::min(b < 16 ? b - 2 : b - 3, 20);
     }
   }
