@@ -6,7 +6,10 @@ i thread-slots per workgroup (the rest of the 256 lanes split j inside the
 workgroup) and the work-item target of the j-split; the kernel variant (one
 or two i-particles per slot, j staged through LDS or broadcast from scalar
 registers) is chosen on the full evaluation.  Results are
-cached as JSON keyed by device architecture, precision and log2(N).
+cached as JSON keyed by device architecture, precision and log2(N).  An entry
+whose values were later set by hand, from sweeps of the calls or steps that it
+serves, names those fields, the day and what was timed under "by_hand"; its
+"measured" is the day of the tuner's own run, which a new run replaces whole.
 
 Ensembles of many clusters are tuned apart (--ensemble C): a block step of
 an ensemble spreads over every cluster, so its time is set by the longest
@@ -39,7 +42,7 @@ import numpy as np
 from . import binding, ics
 
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
-SLOT_CHOICES = (1, 4, 16, 64, 256)
+SLOT_CHOICES = (1, 2, 4, 8, 16, 32, 64, 256)
 TARGET_CHOICES = (256, 1024, 2048, 4096, 8192, 32768, 131072)
 
 
@@ -208,7 +211,7 @@ def tune_ensemble(n_clusters: int, precision: int, n_min: int = 256, n_max: int 
         g = binding.NBody(m[:64], x[:64], v[:64], precision=precision)
         base = g.get_tuning()
         g.close()
-    base = {k: val for k, val in base.items() if k != "measured"}
+    base = {k: val for k, val in base.items() if k not in ("measured", "by_hand")}
 
     def run(tr):
         best = math.inf

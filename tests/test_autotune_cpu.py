@@ -72,3 +72,14 @@ def test_shipped_cache_is_valid():
         # the binding turns every entry into the ABI struct
         tt = binding.Tuning.from_dict(t)
         assert tt.variant == t["variant"]
+
+
+def test_shipped_slots_are_ones_the_tuner_searches():
+    with open(autotune.DEFAULT_CACHE) as f:
+        cache = json.load(f)
+    for key, t in cache.items():
+        assert set(t["i_slots"]) <= set(autotune.SLOT_CHOICES), key
+        hand = t.get("by_hand")
+        if hand:
+            assert hand["day"] and hand["timed"], key
+            assert {f.split("[")[0] for f in hand["fields"]} <= set(t), key
