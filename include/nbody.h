@@ -310,8 +310,9 @@ const char *nbody_last_error(void);
  * (j records read into scalar registers) for evaluations with at least
  * n_j / 16 active particles and i_slots = 256 in every cluster, with one or
  * two i per lane (the LDS kernel with the same K takes the others;
- * nbody_forces and nbody_accel of one cluster use it from 256 entries on in
- * the mixed forms and acceleration-only, from 1024 in FP64).  All
+ * nbody_forces and nbody_accel of one cluster use it from fewer on: in FP64
+ * from 1024 entries, the mixed forms from 2048 and 2^29 pairs, acceleration-only
+ * from 2048 and 2^28, double-single 2^29).  All
  * variants with the same K give bitwise-identical results.
  * Zero fields keep the defaults. */
 #define NBODY_TUNE_BUCKETS 25

@@ -204,11 +204,13 @@ bool is_mixed(int precision) {
 nbody_tuning default_tuning(int precision) {
   nbody_tuning t;
   std::memset(&t, 0, sizeof t);
-  // one i per lane from scalar registers in every precision: items of 64
-  // i-slots, which fill the chip where two i per lane leave it idle (FP64,
-  // full evaluations: 4.33 against 4.37 ms at 2^16, 69.0 against 68.6 ms at
-  // 2^18).  The lighter acceleration-only loops prefer two in the
-  // FP64-difference form (1.82 against 2.12 ms at 2^16).
+  // from scalar registers, one i per lane, in every precision.  FP64: two fill
+  // fewer of the lanes of a small active set (100 of 4096: 19.0 us with one,
+  // 23.8 with two) and are no faster on a large one (all of 2^14 311 against
+  // 318 us, 2^16 4.32 ms both, 2^18 67.6 against 67.5 ms; 1000 of 2^18, 327
+  // against 310 us, is the exception).  The lighter acceleration-only loop of
+  // the FP64-difference form takes two, for the drivers' evaluations (all of
+  // 4096 59 -> 55 us, 2^16 1.79 -> 1.75 ms; 100 of 2^18 53 -> 69 us).
   t.variant = NBODY_VARIANT_S1;
   t.acc_variant = precision == NBODY_MIXED ? NBODY_VARIANT_S2 : 0;
   t.use_graph = NBODY_GRAPH_ON;

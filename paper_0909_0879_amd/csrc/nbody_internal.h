@@ -70,7 +70,7 @@ struct ClusterPlan {
   int32_t S;        // j splits
   int32_t na;       // active particles of the cluster
   int32_t act_off;  // their offset in the active list
-  int32_t tiles;    // i tiles = ceil(na / (P * K))
+  int32_t tiles;    // i tiles = ceil(na / (Pt * K))
   int32_t items;    // tiles * S
   int64_t row_off;  // first partial row of the cluster
   int64_t jb, je;   // j range [jb, je)
@@ -78,8 +78,9 @@ struct ClusterPlan {
   int64_t t_pred;   // tick every particle of the cluster is predicted to
   int32_t small;    // small mixed block step (kSmallStep, Tuning::small_work):
                     // evaluated by the FP64 kernel, never re-evaluated
-  int32_t glog;     // log2 of the lanes that sum one entry's S rows
-                    // (the power of two >= S, at most 64)
+  int32_t glog;     // log2 of the lanes that sum one entry's S rows (the
+                    // power of two >= S, at most 64, and fewer where all the
+                    // entries together would take more than 2^17)
 };
 
 struct Tuning {     // device copy of the launch policy (passed by value)
@@ -93,10 +94,11 @@ struct Tuning {     // device copy of the launch policy (passed by value)
                         // interactions, or kSmallStep active; < 0: none
 };
 
-// Plan kinds (k_plan): which time the particles are predicted to, where the
-// j range comes from, and whether the step is committed.
+// Plan kinds (k_plan, plan_single): which time the particles are predicted to
+// and where the j range comes from.
 enum PlanKind : int {
-  kPlanStep = 0,     // block step: predict to T_next, commit T = T_next, count
+  kPlanStep = 0,     // block step: predict to T_next, count; k_plan commits
+                     // T = T_next, after plan_single the corrector's launch
   kPlanState = 1,    // init / energy: predict to T
   kPlanApi = 2,      // nbody_forces: caller's j arrays
   kPlanRefine = 3,   // FP64 re-evaluation inside a block step (T_next)

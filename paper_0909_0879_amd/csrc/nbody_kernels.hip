@@ -1415,11 +1415,15 @@ __device__ ClusterPlan plan_cluster(const Dev &d, const Tuning &tu, int kind, in
     // workgroups: 6.77 -> 6.60 ms a two-pass evaluation; 20000 of 2^18:
     // 8.54 -> 8.01 ms), but reads each record four times as often through
     // the scalar cache and pays an item's start and end on a quarter of the
-    // pairs: with 256-record chunks all of 2^14 took 703 us against 568, and
-    // all of 2^20 (131072 items) 1554 ms against 1548.  So it needs chunks of
-    // 4 kTJ, or too few items to fill the chip (N = 1000: 170 -> 99 us; N =
-    // 4096, one item a CU, double-single: 151 -> 139 us, acceleration only 66
-    // -> 57), and is left where the items are many anyway.
+    // pairs: with 256-record chunks all of 2^14 took 703 us against 568.  So it
+    // needs chunks of 4 kTJ, or too few items to fill the chip (N = 1000:
+    // 170 -> 99 us; N = 4096, one item a CU, double-single: 151 -> 139 us,
+    // acceleration only 66 -> 57), and is left where the items are many anyway:
+    // with 131072 of them (all of 2^20) it changes FP64 and mixed by less than
+    // 0.3 %, but double-single accelerations from 411 to 440 ms; with 32768
+    // (all of 2^18) it gains 1 to 3 % in FP64 and mixed and costs 2 % in the
+    // double-single accelerations; with 65536 (all of 2^19) it is within 0.5 %
+    // either way.
     const bool share_j = chunk >= 4 * kTJ || tiles * S <= kFewItems;
     p.Pt = (P == kWG && tiles * S < kWideItems && share_j) ? kBlk : P;
     if (p.Pt != P) tiles = (una + (uint32_t)(kBlk * K) - 1) / (uint32_t)(kBlk * K);
@@ -2575,12 +2579,12 @@ __device__ __forceinline__ void sb_run(
 // The mixed forms with one i per lane: five (96 VGPRs).  Six (80, spilling
 // around the pair loop) took 97.3 against 97.7 ms at 2^18 but 562 against
 // 538 us at 2^14, whose items are short; double-single with four: 8.42
-// against 7.60 ms at 2^16.
+// against 7.60 ms at 2^16.  FP64, acceleration only, two i per lane: five
+// (95 VGPRs; left alone 101 and four): 4200 of 2^16 208 against 216 us, all
+// of it 2.65 against 2.67 ms; one i per lane holds seven either way.
 template <int MODE, int K> struct SbOcc {
-  static constexpr int waves = (mode_near(MODE) && K == 1)       ? 5
-                               : (MODE == kModeFP64 && K == 2)    ? 3
-                               : (MODE == kModeFP64Acc)           ? 5
-                                                                  : 1;
+  static constexpr int waves =
+      ((mode_near(MODE) && K == 1) || MODE == kModeFP64Acc) ? 5 : 1;
 };
 
 template <int MODE, int K>
@@ -2981,8 +2985,9 @@ __global__ __launch_bounds__(kWG) void k_sum_flag(Dev d, const int32_t *list, fl
     }
     d.rflag[k] = flag;
     // per-block counts for the ordered compaction (zeroed before this
-    // evaluation's force launches, by the record kernel or, for a block step,
-    // by the step's k_count)
+    // evaluation's force launches: by the record kernel, or the launch that
+    // stands in for it: k_api_single, k_sym_kick_drift, a block step's k_count
+    // or k_step_head)
     if (flag) {
       if constexpr (APPEND) {
         const int r = atomicAdd(&d.sync[0], 1);
