@@ -311,8 +311,7 @@ const char *nbody_last_error(void);
  * n_j / 16 active particles and i_slots = 256 in every cluster, with one or
  * two i per lane (the LDS kernel with the same K takes the others;
  * nbody_forces and nbody_accel of one cluster use it from fewer on: in FP64
- * from 1024 entries, the mixed forms from 2048 and 2^29 pairs, acceleration-only
- * from 2048 and 2^28, double-single 2^29).  All
+ * from 1024 entries, elsewhere from 2048 and 2^27 to 2^29 pairs).  All
  * variants with the same K give bitwise-identical results.
  * Zero fields keep the defaults. */
 #define NBODY_TUNE_BUCKETS 25

@@ -432,17 +432,20 @@ Route state_route(const nbody_ctx *c, bool acc_only) {
 // takes them, from fewer.  With jerk in FP64 from four wide items' worth on
 // (3000 of 2^16: 252 us broadcast, 262 with the tile fill).  Elsewhere the tile
 // fill converts a j so cheaply that it takes eight of them and enough pairs to
-// carry the record launch: mixed 1001 of 2^18 522 us filled against 553, 2100
-// of it 1058 against 976; double-single, acceleration only, 2100 of 2^16 116
-// against 140; the other two, acceleration only, from half as many pairs
-// (mixed 2100 of 2^17 202 against 196, 3000 of 2^16 141 against 152).
+// carry the record launch.  With jerk, mixed: 1001 of 2^18 522 us filled
+// against 553, 3000 of 2^17 732 against 764, 2100 of 2^18 1058 against 976;
+// double-single: 3000 of 2^16 493 against 470, 2100 of it 379 against 391.
+// Acceleration only, double-single: 2100 of 2^16 116 against 140, 3000 of 2^17
+// 251 against 265, 4200 of 2^18 606 against 576; mixed: 3000 of 2^16 141
+// against 152, 2100 of 2^17 202 against 196.
 Route api_route(const nbody_ctx *c, bool acc_only, int64_t na, int64_t n_j) {
   if (c->C != 1) return kRouteDevice;
   if (n_j > c->d.n) return kRouteRaw;       // the buffer holds d.n records
   const bool wide = c->tune.i_slots[bucket_of(na)] == nbk::kWG && (acc_only ? c->sba : c->sb);
-  const int64_t pairs = (int64_t)1 << (acc_only && c->prec != NBODY_MIXED_DS ? 28 : 29);
+  const bool ds = c->prec == NBODY_MIXED_DS;
+  const int log2_pairs = acc_only ? (ds ? 29 : 28) : (ds ? 27 : 29);
   const bool many = wide && (acc_only || is_mixed(c->prec)
-                                 ? na >= 8 * nbk::kWG && na * n_j >= pairs
+                                 ? na >= 8 * nbk::kWG && na * n_j >= (int64_t)1 << log2_pairs
                                  : na >= 4 * nbk::kWG);
   if (!many && na * 16 < n_j) return kRouteRaw;
   // small systems: the record launch costs more than converting in the fill

@@ -1,7 +1,8 @@
 """nbody_forces / nbody_accel on both sides of the entry counts from which they
 build j records for fewer than one entry in 16 (1024 entries in FP64; elsewhere
-2048 and 2^29 pairs, or 2^28 for FP64 and mixed accelerations), and one wide
-item a CU, where its waves start to share the j.  Against the oracle."""
+2048 and 2^29 pairs, or 2^28 for FP64 and mixed accelerations, 2^27 in
+double-single with jerk), and one wide item a CU, where its waves start to share
+the j.  Against the oracle."""
 import numpy as np
 import pytest
 
@@ -19,7 +20,8 @@ FP64, MIXED, DS = binding.FP64, binding.MIXED, binding.MIXED_DS
     (FP64, 131072, (2047, 2048)),         # acceleration only: 2^28 pairs
     (MIXED, 131072, (2047, 2048)),        # the same
     (MIXED, 262144, (2047, 2048)),        # with jerk: 2^29 pairs
-    (DS, 262144, (2047, 2048)),
+    (DS, 65536, (2047, 2048)),            # the same: 2^27
+    (DS, 262144, (2047, 2048)),           # acceleration only: 2^29
     (MIXED, 4096, (3840, 4096)),          # 240 and 256 items of 256 slots
     (DS, 4096, (3840, 4096)),
 ])
