@@ -36,8 +36,8 @@
 //    in a fixed order, so every result is deterministic;
 //  * FP64 mode accumulates in FP64 and folds at most 256 terms at a time into
 //    a TwoSum (hi, lo) pair; mixed mode does rsqrt, r^-3 and the jerk products in
-//    FP32 and folds the FP32 sums of every 64 j into an FP32 TwoSum
-//    (hi, lo) pair;
+//    FP32 and folds the FP32 sums of every 64 j (a lane's share of a tile in
+//    narrow items: 128 with 128 i-slots) into an FP32 TwoSum (hi, lo) pair;
 //  * the same kernels in acceleration-only modes serve the paper's
 //    symplectic drivers (kick / drift sweeps between evaluations);
 //  * the external Galactic field (Sect. 4) is O(N) and rides in the kernels
