@@ -330,7 +330,10 @@ typedef struct nbody_tuning {
                                acceleration term, bounded by max_j m_j/s_ij,
                                exceeds refine_ratio times their net
                                acceleration are re-evaluated with the FP64
-                               kernel (default 1; < 0 disables) */
+                               kernel (default 1; < 0 disables, and then
+                               near_jerk should be off too: a particle with
+                               more than 16 near pairs in one work item leaves
+                               them to the re-evaluation) */
   int32_t i_slots[NBODY_TUNE_BUCKETS];
   int32_t target_items[NBODY_TUNE_BUCKETS];
   int32_t acc_variant;      /* variant of the acceleration-only evaluations
